@@ -111,6 +111,34 @@ def test_decode_long_cache_splits_rows():
     _check_out(out, di, di.k, di.v, lens, True, "long")
 
 
+@pytest.mark.parametrize("dtype,d,h_q,h_kv", [("bf16", 128, 8, 2), ("bf16", 64, 4, 4),
+                                              ("bf16", 128, 16, 2), ("f32", 128, 4, 2),
+                                              ("f32", 64, 8, 1)])
+def test_decode_splits_with_rising_logits(dtype, d, h_q, h_kv):
+    """Caches of 1 .. 1500 rows cut into splits of 128 and 192 rows (empty splits, a split of one
+    row, whole and partial steps, the appended row alone in its split), with logits that rise from
+    -16 to 16 nats along the rows of every second problem, so that the reference of the weights is
+    raised many times.  A logit of 16 nats from terms of like sign errs by at most
+    (d + 2) 2^-24 16 < 1.3e-4 in the worst order and a few 2^-24 16 = 4e-6 in a blocked one, inside
+    the module's 2e-5 max|v|."""
+    lens = [1500, 128, 127, 1, 383, 1344]
+    di = workloads.draw_decode(dtype, h_q, h_kv, d, 1502, lens, seed=21)
+    G = h_q // h_kv
+    q = evict.decode(di.q, dtype)
+    for p in range(0, len(lens), 2):
+        for g in range(h_kv):
+            u = q[p, g * G]
+            ramp = np.linspace(-16.0, 16.0, lens[p])[:, None] / (di.scale * float(u @ u))
+            rows = (ramp * u[None]).astype(np.float32)
+            di.k[p, g, :lens[p]] = workloads.f32_to_bf16_bits(rows) if dtype == "bf16" else rows
+    for append in (True, False):
+        out, k_after, _ = _run(di, append, "splits")
+        _check_out(out, di, di.k, di.v, lens, append, f"splits {dtype} d={d} G={G}")
+        if append:
+            for p, L in enumerate(lens):
+                np.testing.assert_array_equal(k_after[p, :, L], di.k_new[p])
+
+
 def test_decode_over_the_compacted_cache_of_the_pass():
     """Eviction pass on the GPU (one Mistral layer, L = 3000, B = 64), compaction into blocks with
     room for generated rows, then one decode step; compared with the oracle's compacted rows and
