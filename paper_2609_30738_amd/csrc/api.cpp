@@ -175,7 +175,8 @@ size_t cand_ws_bytes(const kv_problem* pr, const kv::Shape& s, int stride, bool 
 // Selection, and with k_out / v_out the compaction of the selected rows, in one launch; base
 // scores from mu / sigma, or given (score).
 // Where the selection's base scores come from: mu / sigma (with lambda1), given scores, or the
-// candidate lists of kv_window_candidates; with cut_out only the candidate cut runs (lists out).
+// candidate lists of kv_window_candidates; with cut_out the lists are written (and without sel_idx
+// only the candidate cut runs).
 struct ScoreSource {
   const float* mu = nullptr;
   const float* sigma = nullptr;
@@ -248,9 +249,9 @@ int mmr_select_impl(const kv_problem* pr, const ScoreSource& src, const void* k,
   return launch_status(kv::launch_mmr_select(s, a, static_cast<hipStream_t>(stream)));
 }
 
-// kv_window_candidates; with sel (the caller has checked that the window kernel cuts the
-// candidates, every C_p <= kCandSelectMax, and the selection's arguments) the selection of each
-// unit follows its cut in the same launch.
+// kv_window_candidates; with sel (the caller has checked the selection's arguments and, where the
+// window kernel cuts the candidates, that every C_p <= kCandSelectMax) the selection of each unit
+// follows its cut in the same launch.
 int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* k, float scale,
                            const float* lambda1, int32_t sigma_rows, int32_t budget,
                            int32_t cand_mult, int32_t keep_tail, const kv_select_opts* opts,
@@ -291,8 +292,9 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
         s, stream_plan_of(pr, s), q_win, k, scale, lambda1, w_mu, budget, b_dev, cand_mult,
         keep_tail, row_max, row_sum, lists, cmax, stride, reinterpret_cast<uint32_t*>(base + head),
         all, sel, hs));
-  if (sel) return KV_ERR_ARG;  // the selection follows the cut only in the window kernel
-  // the scores into the workspace, then the candidate cut of the selection kernel
+  // the scores into the workspace, then the candidate cut of the selection kernel, with sel followed
+  // by the greedy and the compaction in the same workgroup (one launch less, and the candidates
+  // need not come back from memory)
   float* score = reinterpret_cast<float*>(base + head);
   const size_t score_bytes = align_up((size_t)token_extent(pr) * pr->h_kv * sizeof(float));
   st = kv_window_base_scores(pr, q_win, k, scale, lambda1, w_mu, sigma_rows, row_max, row_sum,
@@ -304,6 +306,10 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   src.cut_out = lists;
   src.cut_max = cmax;
   src.list_stride = stride;
+  if (sel)
+    return mmr_select_impl(pr, src, k, sel->v, sel->lambda2, budget, cand_mult, keep_tail, opts,
+                           sel->sel_idx, sel->sel_score, nullptr, nullptr, sel->k_out, sel->v_out,
+                           stream);
   return mmr_select_impl(pr, src, k, nullptr, nullptr, budget, cand_mult, keep_tail, opts, nullptr,
                          nullptr, nullptr, nullptr, nullptr, nullptr, stream);
 }
@@ -631,8 +637,9 @@ int kv_evict_pass(const kv_problem* pr, const void* q_win, const void* k, const 
   st = check_budget(pr, budget, keep_tail, b_host != nullptr || b_dev != nullptr);
   if (st != KV_OK) return st;
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
-  if (pr->dtype == KV_BF16 && cands_in_window_pass(pr, s, scale, cand_mult) &&
-      stride <= kv::kCandSelectMax) {
+  // one launch for the cut and the selection: in the window kernel up to kCandSelectMax candidates,
+  // in the selection kernel where that cuts them from the scores
+  if (!cands_in_window_pass(pr, s, scale, cand_mult) || stride <= kv::kCandSelectMax) {
     kv::CandSelect sel{lambda2, sel_idx, sel_score, v, k_out, v_out, budget + keep_tail};
     return window_candidates_impl(pr, q_win, k, scale, lambda1, sigma_rows, budget, cand_mult,
                                   keep_tail, opts, row_max, row_sum, ws, ws_bytes, &sel, stream);

@@ -134,8 +134,9 @@ struct SelectArgs {
   // base scores given instead of mu / sigma (then lambda1 and w_mu are unused)
   const float* score = nullptr;
   // a candidate list given instead (cand_in, cand_in_max: as launch_stream_window_cands writes
-  // them, list_stride entries per unit; no pooling), or, with cut_out, only the candidate cut:
-  // each unit's C candidates in the same form and its normaliser into cut_max
+  // them, list_stride entries per unit; no pooling); with cut_out the candidate cut also writes
+  // each unit's C candidates in the same form and its normaliser into cut_max, and with
+  // sel_idx == nullptr nothing follows it
   const uint64_t* cand_in = nullptr;
   const float* cand_in_max = nullptr;
   uint64_t* cut_out = nullptr;

@@ -648,7 +648,7 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
     for (int i = tid; i < list_stride; i += kThreads)
       dst[i] = i < C ? cand_entry(order_key(base_score(cpos[i])), (uint32_t)cpos[i]) : 0ull;
     if (tid == 0) cut_max[blockIdx.x] = den;
-    return;
+    if (!sel_idx) return;  // else the selection follows from the same candidates
   }
   }  // phases 0-2
   __syncthreads();  // the staged score keys are dead from here on: the region takes key rows
