@@ -180,7 +180,8 @@ int kv_window_mu_sigma_ex(const kv_problem* pr, const void* q_win, const void* k
  * bit for bit what kv_window_mu_sigma_ex's mu and sigma give, without those two arrays.  score has
  * the layout of mu (problem p at tok_off[p]*h_kv, [h_kv][L_p], fp32, 16-byte aligned).
  * lambda1: [n_prob] fp32 device.  w_mu: finite (1 for the paper's score).
- * For bf16 batches (w = 32, d in {64, 128}, G in {1, 2, 4}, scale > 0) the scores are formed
+ * For bf16 batches (w = 32 with G in {1, 2, 4}, or w in {8, 16} with G w <= 64; d in {64, 128},
+ * scale > 0) the scores are formed
  * inside the window kernel's second pass, which then writes one array instead of two; with every
  * (problem, kv head) scored by one workgroup no workspace is needed.  Otherwise, and when the
  * one-launch path cannot run, mu and sigma go through the workspace
@@ -289,8 +290,8 @@ int kv_mmr_select_scored(const kv_problem* pr, const float* score, const void* k
  * next call that writes it.  budget, cand_mult, keep_tail and opts (pool must be 1, else
  * KV_ERR_ARG; w_mu and the per-problem budgets as in kv_mmr_select_ex) must be the values later
  * given to kv_mmr_select_candidates.  lambda1: [n_prob] fp32 device.
- * For bf16 batches that kv_window_base_scores scores inside the window kernel's second pass, with
- * cand_mult > 0 and L_p <= 32768, the keys are read once in full, the candidates
+ * For bf16 batches of w = 32 that kv_window_base_scores scores inside the window kernel's second
+ * pass, with cand_mult > 0 and L_p <= 32768, the keys are read once in full, the candidates
  * are cut inside that launch (a second pass revisits only the 32-key tiles whose score bound
  * reaches the cut) and no score is stored; otherwise the scores go through the workspace and the
  * selection kernel's first phases cut the candidates from them.  Calls that overlap on one

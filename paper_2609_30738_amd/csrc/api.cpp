@@ -113,9 +113,7 @@ uint32_t spin_limit() {
 
 // Segment plan of the streaming window kernels for this batch.
 kv::StreamPlan stream_plan_of(const kv_problem* pr, const kv::Shape& s) {
-  int64_t total = 0;
-  for (int p = 0; p < pr->n_prob; ++p) total += (int64_t)pr->h_kv * pr->len_host[p];
-  return kv::stream_plan(s, total);
+  return kv::stream_plan(s, pr->len_host);
 }
 
 // Workspace of the window entry points: the larger of the chunked and the streaming layouts.
@@ -154,11 +152,12 @@ size_t cand_lists_bytes(const kv_problem* pr, int stride) {
   return align_up((size_t)pr->n_prob * pr->h_kv * stride * sizeof(uint64_t));
 }
 
-// Whether kv_window_candidates forms the candidate lists inside the window kernel: every unit one
-// segment of a streaming shape, units of at most kCandMaxLen keys, cand_mult > 0 (the caller has
+// Whether kv_window_candidates forms the candidate lists inside the window kernel: w = 32, every
+// unit one segment of a streaming shape, units of at most kCandMaxLen keys, cand_mult > 0 (the caller has
 // checked the candidate count against the selection's limit).
 bool cands_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale, int32_t cand_mult) {
-  return scores_in_window_pass(pr, s, scale) && cand_mult > 0 && s.max_len <= kv::kCandMaxLen;
+  return s.w == 32 && scores_in_window_pass(pr, s, scale) && cand_mult > 0 &&
+         s.max_len <= kv::kCandMaxLen;
 }
 
 // Workspace of kv_window_candidates: the lists and the units' normalisers, then with the fused
@@ -378,7 +377,7 @@ int kv_window_scores(const kv_problem* pr, const void* q_win, const void* k, flo
     st = launch_status(kv::launch_stream_stats(s, plan, q_win, k, scale, ws, nullptr, nullptr, hs));
     if (st != KV_OK) return st;
     return launch_status(kv::launch_combine_partials(s, ws, plan.seg_keys, plan.max_segs,
-                                                     s.group() * 32, row_max, row_sum, hs));
+                                                     s.row_blocks() * 32, row_max, row_sum, hs));
   }
   return launch_status(kv::launch_window_stats(s, q_win, k, scale, ws, row_max, row_sum, hs));
 }

@@ -36,17 +36,16 @@ hipError_t launch_mu_sigma(const Shape& s, const void* q_win, const void* k, flo
                            const float* row_max, const float* row_sum, float* mu, float* sigma,
                            float* attn, bool sigma_all, hipStream_t stream);
 
-// Streaming two-pass row statistics + mu/sigma (bf16, w = 32, G in {1, 2, 4}, scale > 0): every
-// unit is cut
-// into segments of seg_keys keys (a multiple of 256), one workgroup each, sized so that a batch
-// fills the chip about once; the segment partials (m, z) per window row live in the workspace,
-// [n_units][max_segs][32 G] float2.
+// Streaming two-pass row statistics + mu/sigma (bf16, scale > 0, w = 32 with G in {1, 2, 4} or w in
+// {8, 16} with G w <= 64): every unit is cut into segments of seg_keys keys (a multiple of 256), one
+// workgroup each, sized so that a batch fills the chip about once; the segment partials (m, z) per
+// window row live in the workspace, [n_units][max_segs][32 row_blocks()] float2.
 struct StreamPlan {
   int seg_keys;
   int max_segs;
 };
 bool stream_shape_ok(const Shape& s, float scale);
-StreamPlan stream_plan(const Shape& s, int64_t total_keys);  // total_keys = sum_p h_kv L_p
+StreamPlan stream_plan(const Shape& s, const int32_t* lens_host);
 size_t stream_ws_bytes(const Shape& s, const StreamPlan& plan);
 size_t stream_counter_offset(const Shape& s, const StreamPlan& plan);  // counters after the partials
 // Pass 1: segment partials into ws or, with ws == nullptr (only when plan.max_segs == 1), the

@@ -3,8 +3,10 @@
 // per-segment loops in stream_passes.h): the argument block, the tile geometry, the per-wave key
 // stream into LDS and small wave-level helpers.
 //
-// Streaming window statistics for bf16 caches with w = 32 (section 3.1, Eq. (1), Eq. (3)): two
-// passes over the keys, each a plain stream from HBM with no communication between workgroups.
+// Streaming window statistics for bf16 caches (section 3.1, Eq. (1), Eq. (3)): two passes over the
+// keys, each a plain stream from HBM with no communication between workgroups.  A window of 32 rows
+// fills one MFMA block per head; windows of 8 and 16 put 32 / w heads into a block, padded at the
+// end of the unit (at w = 8 and G = 4 a tile takes a quarter of the matrix and exponential work).
 //
 //   Work item: one segment of `seg_keys` consecutive keys of one (problem, kv head) unit, 512
 //   threads = 8 waves.  Every lane holds the MFMA fragments of its window rows of all G heads of
@@ -95,7 +97,7 @@ struct StreamArgs {
 constexpr int kCandLists = kWaves;  // candidate lists per unit: one per wave of the fused kernel
 
 template <int D, int NB> struct SGeo {
-  static constexpr int R = NB * 32;          // window rows of a unit (G heads x 32)
+  static constexpr int R = NB * 32;          // window rows of a unit (G W, padded to whole blocks)
   static constexpr int NS = D / 16;          // MFMA K steps
   static constexpr int CH = D * 2 / 16;      // 16-byte chunks of a key row
   static constexpr int TE = kTileKeys * D;   // elements of a tile
@@ -255,15 +257,18 @@ template <int D, int NB, int NW, int S> struct KeyStream {
   }
 };
 
-// the unit's window-row fragments of every head (head b, rows b * 32 + l32), all K steps
-template <int D, int NB>
+// the unit's window-row fragments (block b, rows b * 32 + l32), all K steps; with W < 32 the rows
+// past the unit's G W re-read its last one (their results are not used)
+template <int D, int NB, int W = 32>
 __device__ __forceinline__ void load_queries(bf16x8_t (&q)[NB][D / 16], const uint16_t* qg, int l32,
-                                             int half) {
+                                             int half, int rows = NB * 32) {
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
+  for (int b = 0; b < NB; ++b) {
+    const int r = W == 32 ? b * 32 + l32 : min(b * 32 + l32, rows - 1);
 #pragma unroll
     for (int s = 0; s < D / 16; ++s)
-      q[b][s] = *reinterpret_cast<const bf16x8_t*>(qg + (size_t)(b * 32 + l32) * D + 16 * s + 8 * half);
+      q[b][s] = *reinterpret_cast<const bf16x8_t*>(qg + (size_t)r * D + 16 * s + 8 * half);
+  }
 }
 
 // An empty use of every query register: the compiler waits for the query loads here, once,
@@ -301,18 +306,21 @@ inline StreamArgs base_args(const Shape& s, const StreamPlan& plan, const void* 
   return a;
 }
 
-// Launch of either pass for the unit shape of `s` (d in {64, 128}, G in {1, 2, 4}).
-template <template <int, int> class Launch>
-hipError_t launch_for_shape(const Shape& s, const StreamArgs& args, hipStream_t st) {
-  const int G = s.group();
-  if (s.d == 128) {
-    if (G == 4) return Launch<128, 4>::run(s, args, st);
-    if (G == 2) return Launch<128, 2>::run(s, args, st);
-    return Launch<128, 1>::run(s, args, st);
-  }
-  if (G == 4) return Launch<64, 4>::run(s, args, st);
-  if (G == 2) return Launch<64, 2>::run(s, args, st);
-  return Launch<64, 1>::run(s, args, st);
+// Launch of a kernel for the unit shape of `s` (d in {64, 128}; w = 32 with G in {1, 2, 4}, or w in
+// {8, 16} with G w <= 64): NB blocks of 32 window rows, each 32 / W heads.
+template <template <int, int, int> class Launch, class... Extra>
+hipError_t launch_for_shape(const Shape& s, const StreamArgs& args, hipStream_t st, Extra... ex) {
+  const int nb = s.row_blocks();
+  auto blocks = [&](auto dd) -> hipError_t {
+    constexpr int D = decltype(dd)::value;
+    if (s.w == 8) return nb == 1 ? Launch<D, 1, 8>::run(s, args, st, ex...) : Launch<D, 2, 8>::run(s, args, st, ex...);
+    if (s.w == 16) return nb == 1 ? Launch<D, 1, 16>::run(s, args, st, ex...) : Launch<D, 2, 16>::run(s, args, st, ex...);
+    if (nb == 4) return Launch<D, 4, 32>::run(s, args, st, ex...);
+    if (nb == 2) return Launch<D, 2, 32>::run(s, args, st, ex...);
+    return Launch<D, 1, 32>::run(s, args, st, ex...);
+  };
+  if (s.d == 128) return blocks(std::integral_constant<int, 128>{});
+  return blocks(std::integral_constant<int, 64>{});
 }
 
 }  // namespace stream

@@ -11,7 +11,7 @@ namespace {
 // ------------------------------------------------------------------------------------------------
 // Pass 2
 // ------------------------------------------------------------------------------------------------
-template <int D, int NB, bool ALL, int NW, int S>
+template <int D, int NB, int W, bool ALL, int NW, int S>
 __global__ __launch_bounds__(NW * 64, 1) void mu_sigma_stream_kernel(StreamArgs a) {
   using Gm = SGeo<D, NB>;
   constexpr int R = Gm::R, NS = Gm::NS, NT = NW * 64;
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mu_sigma_stream_kernel(StreamArgs 
   // the query loads go first: vector memory operations complete in issue order, so the waits on
   // key tiles below also cover them
   bf16x8_t q[NB][NS];
-  load_queries<D, NB>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * 32 * D, l32, half);
+  load_queries<D, NB, W>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * W * D, l32, half, G * W);
   ks.prologue(my_tiles);
   hold_until_loaded<D, NB>(q);
 
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mu_sigma_stream_kernel(StreamArgs 
   // part, part + P, ... of its row (four loads in flight), then one thread per row merges the P
   // results in a fixed order.
   constexpr int P = NT / R;
-  const size_t ri0 = ((size_t)p * a.h_q + (size_t)g * G) * 32;
+  const size_t ri0 = ((size_t)p * a.h_q + (size_t)g * G) * W;
   if (a.part) {
     const int n_seg = (L + a.seg_keys - 1) / a.seg_keys;
     const int row = threadIdx.x % R, pt = threadIdx.x / R;
@@ -66,35 +66,36 @@ __global__ __launch_bounds__(NW * 64, 1) void mu_sigma_stream_kernel(StreamArgs 
   __syncthreads();
   if (threadIdx.x < R) {
     const size_t ri = ri0 + threadIdx.x;
-    float bv;
+    const bool real_row = W == 32 || threadIdx.x < G * W;  // else padding of the last block
+    float bv = INFINITY;
     if (a.part) {
       float M = mz_part[0][threadIdx.x].x, Z = mz_part[0][threadIdx.x].y;
 #pragma unroll
       for (int pt = 1; pt < P; ++pt) merge_mz(M, Z, mz_part[pt][threadIdx.x].x, mz_part[pt][threadIdx.x].y);
       bv = M + __builtin_log2f(Z);
-      if (seg == 0) {
+      if (seg == 0 && real_row) {
         a.row_max_out[ri] = M * kLn2;
         a.row_sum_out[ri] = Z;
       }
-    } else {
+    } else if (real_row) {
       bv = a.row_max[ri] * kLog2e + __builtin_log2f(a.row_sum[ri]);
     }
-    bsh[threadIdx.x] = bv;
+    bsh[threadIdx.x] = real_row ? bv : INFINITY;
   }
   __syncthreads();
   const size_t stat_base = (size_t)a.tok_off[p] * a.h_kv + (size_t)g * L;
-  mu_sigma_tiles<D, NB, ALL, NW, S>(ks, q, bsh, my_tiles, k1, L, c, inv_g, a.mu + stat_base,
-                                    a.sigma + stat_base, l32, half);
+  mu_sigma_tiles<D, NB, ALL, NW, S, kOutMuSigma, W>(ks, q, bsh, my_tiles, k1, L, c, inv_g, a.mu + stat_base,
+                                    a.sigma + stat_base, l32, half, {}, nullptr, G);
   wait_vmem<0>();  // no load into the ring may outlive the workgroup
 }
 
-template <int D, int NB> struct MuSigmaLaunch {
+template <int D, int NB, int W> struct MuSigmaLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
     // eight waves (two per SIMD), two-tile rings (measured: one wave per SIMD with four-tile rings
     // runs this pass 20 % slower)
     const dim3 grid(args.max_segs, s.h_kv, s.n_prob);
-    if (args.sigma_all) mu_sigma_stream_kernel<D, NB, true, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
-    else mu_sigma_stream_kernel<D, NB, false, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
+    if (args.sigma_all) mu_sigma_stream_kernel<D, NB, W, true, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
+    else mu_sigma_stream_kernel<D, NB, W, false, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
     return hipGetLastError();
   }
 };

@@ -24,7 +24,7 @@ struct NoTileHook {
 // After each tile the hook sees the tile's index in the segment and, for an interior tile, the
 // lane's largest logit (unscaled) of every head over its 16 keys; it issues Hook::kStores vector
 // memory stores per tile, which the stream's waits count.
-template <int D, int NB, int NW, int S, class Hook = NoTileHook>
+template <int D, int NB, int NW, int S, int W = 32, class Hook = NoTileHook>
 __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
                                             const bf16x8_t (&q)[NB][D / 16], int my_tiles, int k1,
                                             int L, float c, int l32, int half, float (&m_run)[NB],
@@ -35,8 +35,8 @@ __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
     m_run[b] = -INFINITY;
     z_run[b] = 0.f;
   }
-  // a tile is interior when none of its keys is masked: t0 + 31 < min(k1, L - 31)
-  const int kedge = min(k1, L - 31);
+  // a tile is interior when none of its keys is masked: t0 + 31 < min(k1, L - W + 1)
+  const int kedge = min(k1, L - W + 1);
   for (int j = 0; j < my_tiles; ++j) {
     bf16x8_t kt[NS];
     ks.template next<Hook::kStores>(kt, j, my_tiles, l32, half);
@@ -63,9 +63,9 @@ __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
       }
       hook.template interior<NB>(ks.tile_index(j), tmax);
     } else {
-      // window row l32 of every head sees keys <= L - 32 + l32; keys >= k1 belong to the next
-      // segment.  The key of register jj is t0 + 4 half + 8 (jj / 4) + (jj % 4).
-      const int thr = min(k1 - 1, L - 32 + l32) - t0 - 4 * half;
+      // window row l32 mod W of a head sees keys <= L - W + l32 mod W; keys >= k1 belong to the
+      // next segment.  The key of register jj is t0 + 4 half + 8 (jj / 4) + (jj % 4).
+      const int thr = min(k1 - 1, L - W + l32 % W) - t0 - 4 * half;
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         f32x16_t d = chain<NS>(kt, q[b]);
@@ -184,28 +184,35 @@ struct Prune {
 
 // Pass 2 over the wave's tiles of a segment: logits again with keys as the MFMA N dimension (a
 // lane holds one key), a = 2^(t - b) with the row normalisers b = M + log2 Z read from bsh, summed
-// over the group's heads, then the mean and the two-pass sample variance over the 32 window rows,
-// stored as mu / sigma (mu_u, sigma_u: the unit's rows).  With ALL the variance runs over all
-// G x 32 (head, row) values: every head's mean and squared deviations over its 32 rows, merged
-// across heads with the pairwise update of Chan, Golub and LeVeque.  With OUT = kOutScore the
+// over the group's heads, then the mean and the two-pass sample variance over the W window rows,
+// stored as mu / sigma (mu_u, sigma_u: the unit's rows).  Register (qq, u) of block b holds unit row
+// 32 b + 8 qq + 4 half + u, which for W = 8, 16, 32 is window row 8 (qq mod W / 8) + 4 half + u: a
+// lane holds W / 2 window rows of every head, and the sum over heads is in-lane (rows past G W have
+// b = +inf, hence a = 0).  With ALL the variance runs over all G W (head, row) values: every head's
+// mean and squared deviations over its W rows, merged across heads with the pairwise update of
+// Chan, Golub and LeVeque.  With OUT = kOutScore the
 // key's base score s = fma(lam1, sigma, w_mu mu) (section 3.2, Eq. (5)) is stored instead, with the
 // same rounding as a score formed later from the stored mu and sigma; with OUT = kOutCand the
 // score is also stored (at pr->score_u) and counted by the candidate state `pr` (keys below
 // n_cand), and the wave stops at its first tile that pr no longer wants.
-template <int D, int NB, bool ALL, int NW, int S, int OUT = kOutMuSigma>
+template <int D, int NB, bool ALL, int NW, int S, int OUT = kOutMuSigma, int W = 32>
 __device__ __forceinline__ void mu_sigma_tiles(const KeyStream<D, NB, NW, S>& ks,
                                                const bf16x8_t (&q)[NB][D / 16], const float* bsh,
                                                int my_tiles, int k1, int L, float c, float inv_g,
                                                float* mu_u, float* sigma_u, int l32, int half,
-                                               ScoreOut so = {}, Prune* pr = nullptr) {
+                                               ScoreOut so = {}, Prune* pr = nullptr, int G = NB) {
   constexpr int kStores = 1;  // global stores per tile (the waits count them)
   const int lane = threadIdx.x & 63;
   constexpr int NS = D / 16;
+  static_assert(W == 8 || W == 16 || W == 32, "whole groups of eight rows per head");
+  constexpr int QW = W / 8;   // register groups of a head
+  constexpr int NR = 4 * QW;  // window rows of a head in a lane
+  const float inv_all = W == 32 ? 1.f / (float)(NB * 32 - 1) : 1.f / (float)(G * W - 1);
   auto tile = [&](const bf16x8_t (&kt)[NS], int t0, auto masked) __attribute__((always_inline)) {
     const int key = t0 + l32;
-    // window row r = 4 half + 8 (j / 4) + (j % 4) of every head sees the key iff key <= L - 32 + r
-    const int thr = key - (L - 32) - 4 * half;
-    float ab[16];
+    // window row r of every head sees the key iff key <= L - W + r
+    const int thr = key - (L - W) - 4 * half;
+    float ab[NR];
     float h_mean = 0.f, h_m2 = 0.f;  // ALL: running mean and squared deviations of the heads so far
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -213,57 +220,67 @@ __device__ __forceinline__ void mu_sigma_tiles(const KeyStream<D, NB, NW, S>& ks
       const f32x16_t d = chain<NS>(q[b], kt);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
-        // window rows 8 qq + 4 half + 0..3 of query head b (read per tile: the registers hold
-        // the queries, the tile and the logit blocks)
+        // unit rows 32 b + 8 qq + 4 half + 0..3 (read per tile: the registers hold the queries, the
+        // tile and the logit blocks)
         const float4 bv = *reinterpret_cast<const float4*>(bsh + b * 32 + 8 * qq + 4 * half);
         const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int j = 4 * qq + u;
           float e = __builtin_amdgcn_exp2f(fmaf(d[j], c, -bb[u]));
-          if (decltype(masked)::value && 8 * qq + u < thr) e = 0.f;
-          ab[j] = b == 0 ? e : ab[j] + e;
+          if (decltype(masked)::value && 8 * (qq % QW) + u < thr) e = 0.f;
+          const int r = 4 * (qq % QW) + u;
+          ab[r] = b == 0 && qq < QW ? e : ab[r] + e;
           eb[j] = e;
         }
       }
       if constexpr (ALL) {
-        float hs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 16; ++j) hs[j & 3] += eb[j];
-        const float mb = sum_halves((hs[0] + hs[1]) + (hs[2] + hs[3])) * (1.f / 32.f);
-        float hv[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int hh = 0; hh < 32 / W; ++hh) {  // the heads of the block
+          const int head = b * (32 / W) + hh;
+          if (W < 32 && head >= G) continue;
+          float hs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const float dl = eb[j] - mb;
-          hv[j & 3] = fmaf(dl, dl, hv[j & 3]);
-        }
-        const float m2b = sum_halves((hv[0] + hv[1]) + (hv[2] + hv[3]));
-        if (b == 0) {
-          h_mean = mb;
-          h_m2 = m2b;
-        } else {  // b heads of 32 rows merged with one more
-          const float dl = mb - h_mean;
-          h_mean = fmaf(dl, 1.f / (float)(b + 1), h_mean);
-          h_m2 += fmaf(dl * dl, 32.f * (float)b / (float)(b + 1), m2b);
+          for (int j = hh * NR; j < hh * NR + NR; ++j) hs[j & 3] += eb[j];
+          const float mb = sum_halves((hs[0] + hs[1]) + (hs[2] + hs[3])) * (1.f / (float)W);
+          float hv[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int j = hh * NR; j < hh * NR + NR; ++j) {
+            const float dl = eb[j] - mb;
+            hv[j & 3] = fmaf(dl, dl, hv[j & 3]);
+          }
+          const float m2b = sum_halves((hv[0] + hv[1]) + (hv[2] + hv[3]));
+          if (head == 0) {
+            h_mean = mb;
+            h_m2 = m2b;
+          } else {  // `head` heads of W rows merged with one more
+            const float dl = mb - h_mean;
+            h_mean = fmaf(dl, 1.f / (float)(head + 1), h_mean);
+            h_m2 += fmaf(dl * dl, (float)W * (float)head / (float)(head + 1), m2b);
+          }
         }
       }
     }
-    // ab[j] = G a[r][key] for the window rows r = acc_row(j, lane); the other 16 are in lane ^ 32
+    // ab[j] = G a[r][key] for this lane's window rows; the other W / 2 are in lane ^ 32
     float sp[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sp[u] = (ab[u] + ab[u + 4]) + (ab[u + 8] + ab[u + 12]);
-    const float mean = sum_halves((sp[0] + sp[1]) + (sp[2] + sp[3])) * (inv_g * (1.f / 32.f));
+    for (int u = 0; u < 4; ++u) {
+      if constexpr (NR == 16) sp[u] = (ab[u] + ab[u + 4]) + (ab[u + 8] + ab[u + 12]);
+      else if constexpr (NR == 8) sp[u] = ab[u] + ab[u + 4];
+      else sp[u] = ab[u];
+    }
+    const float mean = sum_halves((sp[0] + sp[1]) + (sp[2] + sp[3])) * (inv_g * (1.f / (float)W));
     float var;
     if constexpr (ALL) {
-      var = h_m2 * (1.f / (float)(NB * 32 - 1));
+      var = h_m2 * inv_all;
     } else {
       float vp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
+      for (int j = 0; j < NR; ++j) {
         const float dl = fmaf(ab[j], inv_g, -mean);
         vp[j & 3] = fmaf(dl, dl, vp[j & 3]);
       }
-      var = sum_halves((vp[0] + vp[1]) + (vp[2] + vp[3])) * (1.f / 31.f);
+      var = sum_halves((vp[0] + vp[1]) + (vp[2] + vp[3])) * (1.f / (float)(W - 1));
     }
     if constexpr (OUT == kOutScore) {
       // both halves hold the key's mean and variance; half 0 stores (every tile has a key < k1,
@@ -287,7 +304,7 @@ __device__ __forceinline__ void mu_sigma_tiles(const KeyStream<D, NB, NW, S>& ks
     bf16x8_t kt[NS];
     ks.template next<kStores>(kt, j, my_tiles, l32, half);  // stores per tile in flight
     const int t0 = ks.tile_key(j);
-    if (t0 + 31 > L - 32) tile(kt, t0, std::true_type{});
+    if (t0 + 31 > L - W) tile(kt, t0, std::true_type{});
     else tile(kt, t0, std::false_type{});
     if constexpr (OUT == kOutCand) pr->update_cut(lane);
   }

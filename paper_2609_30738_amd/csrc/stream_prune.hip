@@ -577,8 +577,12 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   }
 }
 
-template <int D, int NB> struct PruneLaunch {
+template <int D, int NB, int W> struct PruneLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
+    if constexpr (W != 32) return hipErrorInvalidValue;  // the tile codes hold 32 window rows
+    else return run32(s, args, st);
+  }
+  static hipError_t run32(const Shape& s, const StreamArgs& args, hipStream_t st) {
     const dim3 grid(1, s.h_kv, s.n_prob);
     if (args.sel_idx) {
       if (args.sigma_all) window_prune_kernel<D, NB, true, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args);

@@ -10,7 +10,7 @@ namespace {
 // ------------------------------------------------------------------------------------------------
 // Pass 1
 // ------------------------------------------------------------------------------------------------
-template <int D, int NB, int NW, int S>
+template <int D, int NB, int W, int NW, int S>
 __global__ __launch_bounds__(NW * 64, 1) void stats_stream_kernel(StreamArgs a) {
   using Gm = SGeo<D, NB>;
   constexpr int R = Gm::R, NS = Gm::NS;
@@ -34,12 +34,12 @@ __global__ __launch_bounds__(NW * 64, 1) void stats_stream_kernel(StreamArgs a) 
   // the query loads go first: vector memory operations complete in issue order, so the waits on
   // key tiles below also cover them
   bf16x8_t q[NB][NS];
-  load_queries<D, NB>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * 32 * D, l32, half);
+  load_queries<D, NB, W>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * W * D, l32, half, G * W);
   ks.prologue(my_tiles);
   hold_until_loaded<D, NB>(q);
 
   float m_run[NB], z_run[NB];
-  stats_tiles<D, NB, NW, S>(ks, q, my_tiles, k1, L, c, l32, half, m_run, z_run);
+  stats_tiles<D, NB, NW, S, W>(ks, q, my_tiles, k1, L, c, l32, half, m_run, z_run);
   wait_vmem<0>();  // no load into the ring may outlive the workgroup
 
   stats_to_lds<NB>(m_run, z_run, red[wave], l32, half);
@@ -48,18 +48,18 @@ __global__ __launch_bounds__(NW * 64, 1) void stats_stream_kernel(StreamArgs a) 
     const float2 v = merge_waves<NW, R>(&red[0][0], threadIdx.x);
     if (a.part) {
       a.part[(((size_t)p * a.h_kv + g) * a.max_segs + seg) * R + threadIdx.x] = v;
-    } else {  // every unit is one segment: the row statistics themselves
-      const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * 32 + threadIdx.x;
+    } else if (W == 32 || threadIdx.x < G * W) {  // one segment: the row statistics themselves
+      const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * W + threadIdx.x;
       a.row_max_out[ri] = v.x * kLn2;
       a.row_sum_out[ri] = v.y;
     }
   }
 }
 
-template <int D, int NB> struct StatsLaunch {
+template <int D, int NB, int W> struct StatsLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
     const dim3 grid(args.max_segs, s.h_kv, s.n_prob);
-    stats_stream_kernel<D, NB, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
+    stats_stream_kernel<D, NB, W, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
     return hipGetLastError();
   }
 };

@@ -14,7 +14,7 @@ namespace kv {
 namespace stream {
 namespace {
 
-template <int D, int NB, bool ALL, int NW, int S, int OUT>
+template <int D, int NB, int W, bool ALL, int NW, int S, int OUT>
 __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a) {
   using Gm = SGeo<D, NB>;
   constexpr int R = Gm::R, NS = Gm::NS;
@@ -38,12 +38,12 @@ __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a)
   // the query loads go first: vector memory operations complete in issue order, so the waits on
   // key tiles below also cover them
   bf16x8_t q[NB][NS];
-  load_queries<D, NB>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * 32 * D, l32, half);
+  load_queries<D, NB, W>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * W * D, l32, half, G * W);
   ks.prologue(my_tiles);
   hold_until_loaded<D, NB>(q);
 
   float m_run[NB], z_run[NB];
-  stats_tiles<D, NB, NW, S>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run);
+  stats_tiles<D, NB, NW, S, W>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run);
   // every load of pass 1 has landed and been read (its last wait is vmcnt(0)): the ring takes the
   // first tiles of pass 2 while the statistics are merged
   ks.prologue(my_tiles);
@@ -51,36 +51,37 @@ __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a)
   __syncthreads();
   if (threadIdx.x < R) {
     const float2 v = merge_waves<NW, R>(&red[0][0], threadIdx.x);
-    bsh[threadIdx.x] = v.x + __builtin_log2f(v.y);  // b = M + log2 Z, base 2
+    // b = M + log2 Z, base 2; +inf in the padding of the last block
+    bsh[threadIdx.x] = W == 32 || threadIdx.x < G * W ? v.x + __builtin_log2f(v.y) : INFINITY;
   }
   __syncthreads();
   if constexpr (OUT == kOutScore) {
     const ScoreOut so{a.score + stat_base, a.lambda1[p], a.w_mu};
-    mu_sigma_tiles<D, NB, ALL, NW, S, kOutScore>(ks, q, bsh, my_tiles, L, L, c, inv_g, nullptr,
-                                                 nullptr, l32, half, so);
+    mu_sigma_tiles<D, NB, ALL, NW, S, kOutScore, W>(ks, q, bsh, my_tiles, L, L, c, inv_g, nullptr,
+                                                 nullptr, l32, half, so, nullptr, G);
   } else {
-    mu_sigma_tiles<D, NB, ALL, NW, S>(ks, q, bsh, my_tiles, L, L, c, inv_g, a.mu + stat_base,
-                                      a.sigma + stat_base, l32, half);
+    mu_sigma_tiles<D, NB, ALL, NW, S, kOutMuSigma, W>(ks, q, bsh, my_tiles, L, L, c, inv_g, a.mu + stat_base,
+                                      a.sigma + stat_base, l32, half, {}, nullptr, G);
   }
   wait_vmem<0>();  // no load into the ring may outlive the workgroup
   // the row statistics, merged again from the same entries in the same order
-  if (threadIdx.x < R) {
+  if (threadIdx.x < (W == 32 ? R : G * W)) {
     const float2 v = merge_waves<NW, R>(&red[0][0], threadIdx.x);
-    const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * 32 + threadIdx.x;
+    const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * W + threadIdx.x;
     a.row_max_out[ri] = v.x * kLn2;
     a.row_sum_out[ri] = v.y;
   }
 }
 
-template <int D, int NB> struct WindowLaunch {
+template <int D, int NB, int W> struct WindowLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
     const dim3 grid(1, s.h_kv, s.n_prob);
     if (args.score) {
-      if (args.sigma_all) window_stream_kernel<D, NB, true, kWaves, 2, kOutScore><<<grid, kThreads, 0, st>>>(args);
-      else window_stream_kernel<D, NB, false, kWaves, 2, kOutScore><<<grid, kThreads, 0, st>>>(args);
+      if (args.sigma_all) window_stream_kernel<D, NB, W, true, kWaves, 2, kOutScore><<<grid, kThreads, 0, st>>>(args);
+      else window_stream_kernel<D, NB, W, false, kWaves, 2, kOutScore><<<grid, kThreads, 0, st>>>(args);
     } else {
-      if (args.sigma_all) window_stream_kernel<D, NB, true, kWaves, 2, kOutMuSigma><<<grid, kThreads, 0, st>>>(args);
-      else window_stream_kernel<D, NB, false, kWaves, 2, kOutMuSigma><<<grid, kThreads, 0, st>>>(args);
+      if (args.sigma_all) window_stream_kernel<D, NB, W, true, kWaves, 2, kOutMuSigma><<<grid, kThreads, 0, st>>>(args);
+      else window_stream_kernel<D, NB, W, false, kWaves, 2, kOutMuSigma><<<grid, kThreads, 0, st>>>(args);
     }
     return hipGetLastError();
   }

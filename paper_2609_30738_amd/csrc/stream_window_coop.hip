@@ -28,7 +28,7 @@ __device__ __forceinline__ float2 load_partial(const float2* src) {
 
 // In base-score mode (SC) pass 2 stores each key's base score instead of mu and sigma (see
 // stream_window.hip).
-template <int D, int NB, bool ALL, int NW, int S, bool SC>
+template <int D, int NB, int W, bool ALL, int NW, int S, bool SC>
 __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, uint32_t* arrive,
                                                                  uint32_t spin_limit) {
   using Gm = SGeo<D, NB>;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
   const int my_tiles = tiles_of(k0, k1);
 
   bf16x8_t q[NB][NS];
-  load_queries<D, NB>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * 32 * D, l32, half);
+  load_queries<D, NB, W>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * W * D, l32, half, G * W);
   ks.prologue(my_tiles);
   hold_until_loaded<D, NB>(q);
 
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
   // with device-coherent stores, complete before the workgroup leaves the final barrier
   auto pass1 = [&](const KeyStream<D, NB, NW, S>& st, int sg, int s1, int n_my) {
     float m_run[NB], z_run[NB];
-    stats_tiles<D, NB, NW, S>(st, q, n_my, s1, L, c, l32, half, m_run, z_run);
+    stats_tiles<D, NB, NW, S, W>(st, q, n_my, s1, L, c, l32, half, m_run, z_run);
     stats_to_lds<NB>(m_run, z_run, red[wave], l32, half);
     __syncthreads();
     if (threadIdx.x < R) store_partial(part_u + (size_t)sg * R + threadIdx.x, merge_waves<NW, R>(&red[0][0], threadIdx.x));
@@ -132,9 +132,10 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
     float M = mz_part[0][threadIdx.x].x, Z = mz_part[0][threadIdx.x].y;
 #pragma unroll
     for (int pt = 1; pt < P; ++pt) merge_mz(M, Z, mz_part[pt][threadIdx.x].x, mz_part[pt][threadIdx.x].y);
-    bsh[threadIdx.x] = M + __builtin_log2f(Z);
-    if (seg == 0) {
-      const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * 32 + threadIdx.x;
+    const bool real_row = W == 32 || threadIdx.x < G * W;  // else padding of the last block
+    bsh[threadIdx.x] = real_row ? M + __builtin_log2f(Z) : INFINITY;
+    if (seg == 0 && real_row) {
+      const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * W + threadIdx.x;
       a.row_max_out[ri] = M * kLn2;
       a.row_sum_out[ri] = Z;
     }
@@ -142,11 +143,11 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
   __syncthreads();
   if constexpr (SC) {
     const ScoreOut so{a.score + stat_base, a.lambda1[p], a.w_mu};
-    mu_sigma_tiles<D, NB, ALL, NW, S, kOutScore>(ks, q, bsh, my_tiles, k1, L, c, inv_g, nullptr, nullptr,
-                                            l32, half, so);
+    mu_sigma_tiles<D, NB, ALL, NW, S, kOutScore, W>(ks, q, bsh, my_tiles, k1, L, c, inv_g, nullptr, nullptr,
+                                            l32, half, so, nullptr, G);
   } else {
-    mu_sigma_tiles<D, NB, ALL, NW, S>(ks, q, bsh, my_tiles, k1, L, c, inv_g, a.mu + stat_base,
-                                      a.sigma + stat_base, l32, half);
+    mu_sigma_tiles<D, NB, ALL, NW, S, kOutMuSigma, W>(ks, q, bsh, my_tiles, k1, L, c, inv_g, a.mu + stat_base,
+                                      a.sigma + stat_base, l32, half, {}, nullptr, G);
   }
   wait_vmem<0>();  // no load into the ring may outlive the workgroup
 }
@@ -159,12 +160,12 @@ __global__ void zero_words_kernel(uint32_t* w, int n) {
 // One launch of window_coop_kernel after its counters are cleared.  Used when the whole grid fits
 // the chip at once (then no workgroup normally waits long); `launched` tells the caller whether it
 // ran.
-template <int D, int NB> struct CoopLaunch {
+template <int D, int NB, int W> struct CoopLaunch {
   template <bool ALL, bool SC> static const void* kernel() {
-    return reinterpret_cast<const void*>(window_coop_kernel<D, NB, ALL, kWaves, 2, SC>);
+    return reinterpret_cast<const void*>(window_coop_kernel<D, NB, W, ALL, kWaves, 2, SC>);
   }
-  static hipError_t run(const Shape& s, StreamArgs args, uint32_t* arrive, uint32_t spin_limit,
-                        hipStream_t st, bool* launched) {
+  static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st, uint32_t* arrive,
+                        uint32_t spin_limit, bool* launched) {
     const bool sc = args.score != nullptr;
     const void* kern = args.sigma_all ? (sc ? kernel<true, true>() : kernel<true, false>())
                                       : (sc ? kernel<false, true>() : kernel<false, false>());
@@ -181,11 +182,11 @@ template <int D, int NB> struct CoopLaunch {
     const int n_units = s.n_prob * s.h_kv;
     zero_words_kernel<<<(n_units + 255) / 256, 256, 0, st>>>(arrive, n_units);
     if (args.sigma_all) {
-      if (sc) window_coop_kernel<D, NB, true, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-      else window_coop_kernel<D, NB, true, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
+      if (sc) window_coop_kernel<D, NB, W, true, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
+      else window_coop_kernel<D, NB, W, true, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
     } else {
-      if (sc) window_coop_kernel<D, NB, false, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-      else window_coop_kernel<D, NB, false, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
+      if (sc) window_coop_kernel<D, NB, W, false, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
+      else window_coop_kernel<D, NB, W, false, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
     }
     e = hipGetLastError();
     *launched = e == hipSuccess;
@@ -215,16 +216,7 @@ hipError_t launch_stream_window_coop(const Shape& s, const StreamPlan& plan, con
     a.w_mu = sm->w_mu;
   }
   uint32_t* arrive = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_counter_offset(s, plan));
-  const int G = s.group();
-  using namespace stream;
-  if (s.d == 128) {
-    if (G == 4) return CoopLaunch<128, 4>::run(s, a, arrive, spin_limit, stream, launched);
-    if (G == 2) return CoopLaunch<128, 2>::run(s, a, arrive, spin_limit, stream, launched);
-    return CoopLaunch<128, 1>::run(s, a, arrive, spin_limit, stream, launched);
-  }
-  if (G == 4) return CoopLaunch<64, 4>::run(s, a, arrive, spin_limit, stream, launched);
-  if (G == 2) return CoopLaunch<64, 2>::run(s, a, arrive, spin_limit, stream, launched);
-  return CoopLaunch<64, 1>::run(s, a, arrive, spin_limit, stream, launched);
+  return stream::launch_for_shape<stream::CoopLaunch>(s, a, stream, arrive, spin_limit, launched);
 }
 
 }  // namespace kv

@@ -344,6 +344,29 @@ def test_stream_shapes_one_segment_per_unit(h_q, h_kv, d):
     _all(gpu_cases.run_gpu(wl, fused=True))
 
 
+@pytest.mark.parametrize("h_q,h_kv,d,w", [(8, 2, 128, 8), (14, 2, 64, 8), (2, 2, 128, 8),
+                                          (4, 2, 64, 16), (6, 2, 128, 16), (8, 2, 64, 16)])
+@pytest.mark.parametrize("lens,n_layers", [([1000, 531, 41], 1), ([5003, 300], 2), ([3001], 80)])
+def test_short_windows(h_q, h_kv, d, w, lens, n_layers, monkeypatch):
+    """bf16 windows of 8 and 16 rows, whole and padded 32-row blocks (G w = 8 .. 56), both
+    dispersion readings: units of one segment and of several (ragged, partial tiles), the
+    workgroup that computes late segments itself, and 160 units over the chip's CUs."""
+    import dataclasses
+    wl = dataclasses.replace(_shape_workload(h_q, h_kv, d, len(lens), n_layers, lens), w=w,
+                             name=f"bf16_hq{h_q}_d{d}_W{w}_L{lens}")
+    probs = [0] if n_layers > 2 else None
+    for sigma_rows in ("group_mean", "all_rows"):
+        monkeypatch.delenv("KVEVICT_SPIN_LIMIT", raising=False)
+        run = gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows)
+        print("  ", gpu_cases.summarize(gpu_cases.check_all(run, js=probs)), flush=True)
+        if n_layers > 2:
+            continue
+        monkeypatch.setenv("KVEVICT_SPIN_LIMIT", "0")
+        late = gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows)
+        for name in ("row_max", "row_sum", "score", "sel_idx", "k_out", "v_out"):
+            assert np.array_equal(run.host[name], late.host[name]), name
+
+
 def test_segments_merged_by_the_second_launch():
     """192 units of 5000 keys in two segments each: 384 workgroups do not fit the chip at once, so
     the fused entry point takes two launches, the second merging the first's segment partials
