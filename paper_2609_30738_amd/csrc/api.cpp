@@ -116,6 +116,15 @@ kv::StreamPlan stream_plan_of(const kv_problem* pr, const kv::Shape& s) {
   return kv::stream_plan(s, pr->len_host);
 }
 
+// The plan of the candidate kernel (max_cand: the largest C_p).  Its second pass revisits the tiles
+// that can hold a candidate, few where tiles far outnumber candidates: then a unit is read little
+// more than once, and whole units pay even where they leave CUs idle (128 units of 30000 keys:
+// 405 us as two workgroups each through base scores, 310 whole).  Where every second tile can hold
+// a candidate they do not (112 units of 8000 keys, C = 256: 190 and 226 us).
+kv::StreamPlan cand_plan_of(const kv_problem* pr, const kv::Shape& s, int max_cand) {
+  return kv::stream_plan(s, pr->len_host, s.max_len / 32 >= 2 * max_cand);
+}
+
 // Workspace of the window entry points: the larger of the chunked and the streaming layouts.
 size_t window_ws_bytes(const kv_problem* pr, const kv::Shape& s) {
   size_t b = kv::window_stats_ws_bytes(s);
@@ -133,9 +142,9 @@ int64_t token_extent(const kv_problem* pr) {
 }
 
 // Whether kv_window_base_scores forms the scores inside the window kernel's second pass (bf16
-// streaming shapes with every unit one segment), or from mu / sigma in the workspace.
+// streaming shapes with every unit in one workgroup), or from mu / sigma in the workspace.
 bool scores_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale) {
-  return kv::stream_shape_ok(s, scale) && stream_plan_of(pr, s).max_segs == 1;
+  return kv::stream_shape_ok(s, scale) && stream_plan_of(pr, s).one_wg();
 }
 
 // Workspace of kv_window_base_scores: none for the fused path (with fused_ok, for a positive
@@ -153,11 +162,12 @@ size_t cand_lists_bytes(const kv_problem* pr, int stride) {
 }
 
 // Whether kv_window_candidates forms the candidate lists inside the window kernel: w = 32, every
-// unit one segment of a streaming shape, units of at most kCandMaxLen keys, cand_mult > 0 (the caller has
+// unit of a streaming shape in one workgroup, units of at most kCandMaxLen keys, cand_mult > 0 (the caller has
 // checked the candidate count against the selection's limit).
-bool cands_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale, int32_t cand_mult) {
-  return s.w == 32 && scores_in_window_pass(pr, s, scale) && cand_mult > 0 &&
-         s.max_len <= kv::kCandMaxLen;
+bool cands_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale, int32_t cand_mult,
+                          int max_cand) {
+  return s.w == 32 && kv::stream_shape_ok(s, scale) && cand_plan_of(pr, s, max_cand).one_wg() &&
+         cand_mult > 0 && s.max_len <= kv::kCandMaxLen;
 }
 
 // Workspace of kv_window_candidates: the lists and the units' normalisers, then with the fused
@@ -275,7 +285,7 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   if (st != KV_OK) return st;
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
   if (stride > kv::select_max_candidates(pr->d, elem_bytes(pr->dtype))) return KV_ERR_SHAPE;
-  const bool fused = cands_in_window_pass(pr, s, scale, cand_mult);
+  const bool fused = cands_in_window_pass(pr, s, scale, cand_mult, stride);
   const size_t need = cand_ws_bytes(pr, s, stride, fused);
   if (ws_bytes < need || !ws || (reinterpret_cast<uintptr_t>(ws) & (kWsAlign - 1)))
     return KV_ERR_WORKSPACE;
@@ -288,7 +298,7 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   const size_t head = cand_lists_bytes(pr, stride) + align_up(n_units * sizeof(float));
   if (fused)
     return launch_status(kv::launch_stream_window_cands(
-        s, stream_plan_of(pr, s), q_win, k, scale, lambda1, w_mu, budget, b_dev, cand_mult,
+        s, cand_plan_of(pr, s, stride), q_win, k, scale, lambda1, w_mu, budget, b_dev, cand_mult,
         keep_tail, row_max, row_sum, lists, cmax, stride, reinterpret_cast<uint32_t*>(base + head),
         all, sel, hs));
   // the scores into the workspace, then the candidate cut of the selection kernel, with sel followed
@@ -433,10 +443,10 @@ int kv_window_mu_sigma_ex(const kv_problem* pr, const void* q_win, const void* k
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (kv::stream_shape_ok(s, scale)) {
     const kv::StreamPlan plan = stream_plan_of(pr, s);
-    if (plan.max_segs == 1)  // every unit one segment: both passes of a unit in one workgroup
+    if (plan.one_wg())  // both passes of a unit in one workgroup
       return launch_status(kv::launch_stream_window(s, plan, q_win, k, scale, row_max, row_sum, mu,
                                                     sigma, all, hs));
-    // several segments per unit: one cooperative launch if the grid fits the chip at once
+    // several workgroups per unit: one cooperative launch if the grid fits the chip at once
     bool launched = false;
     st = launch_status(kv::launch_stream_window_coop(s, plan, q_win, k, scale, ws, row_max, row_sum,
                                                      mu, sigma, all, spin_limit(), hs, &launched));
@@ -578,7 +588,7 @@ size_t kv_candidates_workspace_bytes(const kv_problem* pr, int32_t budget, int32
   if (opts && opts->pool != 1) return 0;
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
   if (stride > kv::select_max_candidates(pr->d, elem_bytes(pr->dtype))) return 0;
-  return cand_ws_bytes(pr, s, stride, cands_in_window_pass(pr, s, 1.f, cand_mult));
+  return cand_ws_bytes(pr, s, stride, cands_in_window_pass(pr, s, 1.f, cand_mult, stride));
 }
 
 int kv_window_candidates(const kv_problem* pr, const void* q_win, const void* k, float scale,
@@ -638,7 +648,7 @@ int kv_evict_pass(const kv_problem* pr, const void* q_win, const void* k, const 
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
   // one launch for the cut and the selection: in the window kernel up to kCandSelectMax candidates,
   // in the selection kernel where that cuts them from the scores
-  if (!cands_in_window_pass(pr, s, scale, cand_mult) || stride <= kv::kCandSelectMax) {
+  if (!cands_in_window_pass(pr, s, scale, cand_mult, stride) || stride <= kv::kCandSelectMax) {
     kv::CandSelect sel{lambda2, sel_idx, sel_score, v, k_out, v_out, budget + keep_tail};
     return window_candidates_impl(pr, q_win, k, scale, lambda1, sigma_rows, budget, cand_mult,
                                   keep_tail, opts, row_max, row_sum, ws, ws_bytes, &sel, stream);

@@ -36,16 +36,27 @@ hipError_t launch_mu_sigma(const Shape& s, const void* q_win, const void* k, flo
                            const float* row_max, const float* row_sum, float* mu, float* sigma,
                            float* attn, bool sigma_all, hipStream_t stream);
 
+constexpr int kStreamMaxPerWg = 3;  // segments whose statistics a one-workgroup unit can hold
+
 // Streaming two-pass row statistics + mu/sigma (bf16, scale > 0, w = 32 with G in {1, 2, 4} or w in
 // {8, 16} with G w <= 64): every unit is cut into segments of seg_keys keys (a multiple of 256), one
 // workgroup each, sized so that a batch fills the chip about once; the segment partials (m, z) per
 // window row live in the workspace, [n_units][max_segs][32 row_blocks()] float2.
+// A workgroup takes `per_wg` consecutive segments of a unit (statistics are still merged segment by
+// segment, so the results do not depend on it): one where the segments fit the chip at once, else
+// as many as it takes to fit; max_wgs workgroups for the longest unit, n_wgs over the batch.
 struct StreamPlan {
   int seg_keys;
   int max_segs;
+  int per_wg;
+  int max_wgs;
+  int64_t n_wgs;
+  // every unit's keys in one workgroup, which can hold the statistics of per_wg segments
+  bool one_wg() const { return max_wgs == 1 && per_wg <= kStreamMaxPerWg; }
 };
 bool stream_shape_ok(const Shape& s, float scale);
-StreamPlan stream_plan(const Shape& s, const int32_t* lens_host);
+// whole: a whole unit to a workgroup where it can hold the statistics of its segments
+StreamPlan stream_plan(const Shape& s, const int32_t* lens_host, bool whole = false);
 size_t stream_ws_bytes(const Shape& s, const StreamPlan& plan);
 size_t stream_counter_offset(const Shape& s, const StreamPlan& plan);  // counters after the partials
 // Pass 1: segment partials into ws or, with ws == nullptr (only when plan.max_segs == 1), the
@@ -60,18 +71,18 @@ hipError_t launch_stream_mu_sigma(const Shape& s, const StreamPlan& plan, const 
                                   const float* row_max_in, const float* row_sum_in,
                                   float* row_max_out, float* row_sum_out, float* mu, float* sigma,
                                   bool sigma_all, hipStream_t stream);
-// Both passes in one launch when every unit is one segment (plan.max_segs == 1): row_max /
-// row_sum and mu / sigma out, no workspace.
+// Both passes in one launch when every unit is one workgroup (plan.one_wg()): row_max / row_sum
+// and mu / sigma out, no workspace.
 hipError_t launch_stream_window(const Shape& s, const StreamPlan& plan, const void* q_win,
                                 const void* k, float scale, float* row_max, float* row_sum,
                                 float* mu, float* sigma, bool sigma_all, hipStream_t stream);
-// Both passes in one launch, every unit one segment, in base-score mode: row_max / row_sum, and
+// Both passes in one launch, every unit one workgroup, in base-score mode: row_max / row_sum, and
 // per key s = fma(lambda1[p], sigma, w_mu mu) into score instead of mu / sigma.
 hipError_t launch_stream_window_scores(const Shape& s, const StreamPlan& plan, const void* q_win,
                                        const void* k, float scale, const float* lambda1,
                                        float w_mu, float* row_max, float* row_sum, float* score,
                                        bool sigma_all, hipStream_t stream);
-// Window statistics and the candidate set in one launch, every unit one segment (candidate mode,
+// Window statistics and the candidate set in one launch, every unit one workgroup (candidate mode,
 // stream_prune.hip): row_max / row_sum, and per unit the candidate list [n_units][cand_stride] of
 // (order key of the score, position) entries packed as key << 32 | (0xFFFFFFFF - position): the
 // unit's C_p best entries in ascending position order, then zeros; and cand_max [n_units], the

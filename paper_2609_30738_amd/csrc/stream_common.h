@@ -56,6 +56,7 @@ struct StreamArgs {
   int h_q, h_kv;
   float c;  // softmax scale * log2(e)
   int seg_keys, max_segs;
+  int per_wg;  // consecutive segments of a workgroup (the kernels that run both passes)
   float2* part;           // [n_units][max_segs][R] segment partials (m, z), base 2; pass 1 with
                           // part == nullptr (one segment per unit) writes row_max_out / row_sum_out
   const float* row_max;   // pass 2 from given statistics (part == nullptr)
@@ -303,6 +304,7 @@ inline StreamArgs base_args(const Shape& s, const StreamPlan& plan, const void* 
   a.c = scale * kLog2e;
   a.seg_keys = plan.seg_keys;
   a.max_segs = plan.max_segs;
+  a.per_wg = plan.per_wg;
   return a;
 }
 

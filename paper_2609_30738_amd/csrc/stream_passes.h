@@ -17,10 +17,27 @@ struct NoTileHook {
   __device__ __forceinline__ void guarded(int) const {}
 };
 
+// Lanes l and l ^ 32 hold the same rows (different keys): merge them and put the wave's (m, z) of
+// unit row b * 32 + l32 into red[b * 32 + l32].  The caller merges the waves after a barrier.
+template <int NB>
+__device__ __forceinline__ void stats_to_lds(const float (&m_run)[NB], const float (&z_run)[NB],
+                                             float2* red, int l32, int half) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float m = m_run[b], z = z_run[b];
+    merge_mz(m, z, swap_halves(m), swap_halves(z));
+    if (half == 0) red[b * 32 + l32] = make_float2(m, z);
+  }
+}
+
 // Pass 1 over the wave's tiles of a segment [k0, k1) of a unit with L keys: for every head, the
 // running maximum m of t = logit * c and the sum z of 2^(t - m) over the keys the lane's window
 // row sees (online softmax; base 2).  Interior tiles run without masks or branches; a tile with a
 // masked key (the causal triangle of the window, keys past the segment end) takes a guarded path.
+// With seg_dst, the keys are n_segs segments of seg_tiles tiles of the wave (the last one may be
+// shorter): at the end of every segment but the last its statistics go to seg_dst, seg_stride
+// entries further for each, as stats_to_lds leaves them, and the next starts anew, as in a workgroup
+// of its own.
 // After each tile the hook sees the tile's index in the segment and, for an interior tile, the
 // lane's largest logit (unscaled) of every head over its 16 keys; it issues Hook::kStores vector
 // memory stores per tile, which the stream's waits count.
@@ -28,16 +45,28 @@ template <int D, int NB, int NW, int S, int W = 32, class Hook = NoTileHook>
 __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
                                             const bf16x8_t (&q)[NB][D / 16], int my_tiles, int k1,
                                             int L, float c, int l32, int half, float (&m_run)[NB],
-                                            float (&z_run)[NB], const Hook& hook = Hook{}) {
+                                            float (&z_run)[NB], const Hook& hook = Hook{},
+                                            float2* seg_dst = nullptr, int seg_stride = 0,
+                                            int seg_tiles = 0, int n_segs = 1) {
   constexpr int NS = D / 16;
+  auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    m_run[b] = -INFINITY;
-    z_run[b] = 0.f;
-  }
+    for (int b = 0; b < NB; ++b) {
+      m_run[b] = -INFINITY;
+      z_run[b] = 0.f;
+    }
+  };
+  reset();
+  int seg = 0;
+  auto end_segment = [&]() __attribute__((always_inline)) {
+    stats_to_lds<NB>(m_run, z_run, seg_dst + seg * seg_stride, l32, half);
+    reset();
+    ++seg;
+  };
   // a tile is interior when none of its keys is masked: t0 + 31 < min(k1, L - W + 1)
   const int kedge = min(k1, L - W + 1);
   for (int j = 0; j < my_tiles; ++j) {
+    if (seg_dst && j == (seg + 1) * seg_tiles) end_segment();
     bf16x8_t kt[NS];
     ks.template next<Hook::kStores>(kt, j, my_tiles, l32, half);
     const int t0 = ks.tile_key(j);
@@ -88,19 +117,8 @@ __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
       hook.guarded(ks.tile_index(j));
     }
   }
-}
-
-// Lanes l and l ^ 32 hold the same rows (different keys): merge them and put the wave's (m, z) of
-// unit row b * 32 + l32 into red[b * 32 + l32].  The caller merges the waves after a barrier.
-template <int NB>
-__device__ __forceinline__ void stats_to_lds(const float (&m_run)[NB], const float (&z_run)[NB],
-                                             float2* red, int l32, int half) {
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    float m = m_run[b], z = z_run[b];
-    merge_mz(m, z, swap_halves(m), swap_halves(z));
-    if (half == 0) red[b * 32 + l32] = make_float2(m, z);
-  }
+  if (seg_dst)
+    while (seg < n_segs - 1) end_segment();  // no tile of the wave in the last segments
 }
 
 // (m, z) of one row over the NW waves' entries red[w * R + row], merged in wave order
@@ -110,6 +128,23 @@ __device__ __forceinline__ float2 merge_waves(const float2* red, int row) {
 #pragma unroll
   for (int w = 1; w < NW; ++w) merge_mz(v.x, v.y, red[w * R + row].x, red[w * R + row].y);
   return v;
+}
+
+// (m, z) of one row of a unit whose workgroup holds all its segments: the first n_segs - 1 at
+// `first`, seg_stride entries apart, the last at `last`; merged in segment order, as the kernels
+// that take one segment per workgroup do
+template <int NW, int R>
+__device__ __forceinline__ float2 merge_unit(const float2* first, int seg_stride, int n_segs,
+                                             const float2* last, int row) {
+  float M = -INFINITY, Z = 0.f;
+  for (int i = 0; i < n_segs - 1; ++i) {
+    const float2 v = merge_waves<NW, R>(first + i * seg_stride, row);
+    merge_mz(M, Z, v.x, v.y);
+  }
+  const float2 v = merge_waves<NW, R>(last, row);
+  if (n_segs == 1) return v;
+  merge_mz(M, Z, v.x, v.y);
+  return make_float2(M, Z);
 }
 
 // One mu or sigma value to HBM with the device-scope store policy (sc1).  These 128-byte pieces

@@ -11,12 +11,17 @@ bool stream_shape_ok(const Shape& s, float scale) {
   return s.dtype == kDtBf16 && window && (s.d == 64 || s.d == 128) && scale > 0.f;
 }
 
-StreamPlan stream_plan(const Shape& s, const int32_t* lens) {
+StreamPlan stream_plan(const Shape& s, const int32_t* lens, bool whole) {
   // about one segment per compute unit (256 on MI355X), whole 256-key steps of the eight waves
   constexpr int64_t kTarget = 256, kStep = stream::kWaves * stream::kTileKeys;
   const int64_t max_seg = ((int64_t)s.max_len + kStep - 1) / kStep * kStep;
   int64_t total = 0;
   for (int p = 0; p < s.n_prob; ++p) total += (int64_t)s.h_kv * lens[p];
+  auto work_items = [&](int64_t keys) {  // workgroups that take `keys` keys each
+    int64_t n = 0;
+    for (int p = 0; p < s.n_prob; ++p) n += s.h_kv * ((lens[p] + keys - 1) / keys);
+    return n;
+  };
   int64_t seg = ((total + kTarget - 1) / kTarget + kStep - 1) / kStep * kStep;
   if (s.w == 32) {
     // four tiles per wave at least: shorter segments cost more in exchanges than they save
@@ -28,17 +33,17 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens) {
     // the chip's CUs would cost a second round: then longer segments (160 units of 2500 keys whole
     // 37 us, as 320 segments 58)
     seg = std::min(std::max<int64_t>(s.max_len <= 1024 ? 1024 : kStep, seg), max_seg);
-    auto work_items = [&](int64_t keys) {
-      int64_t n = 0;
-      for (int p = 0; p < s.n_prob; ++p) n += s.h_kv * ((lens[p] + keys - 1) / keys);
-      return n;
-    };
     while (seg < max_seg && work_items(seg) > kTarget)
       seg = std::min(max_seg, seg + std::max<int64_t>(kStep, seg / 16 / kStep * kStep));
   }
   StreamPlan plan;
   plan.seg_keys = (int)seg;
   plan.max_segs = (int)(((int64_t)s.max_len + seg - 1) / seg);
+  // segments over the chip's CUs go to workgroups of several, as few as it takes to fit
+  plan.per_wg = whole && plan.max_segs <= kStreamMaxPerWg ? plan.max_segs : 1;
+  while (plan.per_wg < plan.max_segs && work_items(seg * plan.per_wg) > kTarget) ++plan.per_wg;
+  plan.max_wgs = (plan.max_segs + plan.per_wg - 1) / plan.per_wg;
+  plan.n_wgs = work_items(seg * plan.per_wg);
   return plan;
 }
 

@@ -193,8 +193,10 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   // pass 1: the tile's largest t; from the order on: the bound of the i-th tile of the order
   __shared__ float ub[kPruneMaxTiles];
   __shared__ uint16_t order[kPruneMaxTiles];
-  // the bin counts and offsets of the order
-  __shared__ uint32_t bins[2 * kOrderBins];
+  // pass 1: the statistics of the unit's segments but the last; then the bin counts and offsets of
+  // the order
+  constexpr int kSegWords = (kStreamMaxPerWg - 1) * kRedWords;
+  __shared__ __align__(16) uint32_t bins[kSegWords > 2 * kOrderBins ? kSegWords : 2 * kOrderBins];
   __shared__ float c_max[NW];
   __shared__ uint32_t ev[NW];
   __shared__ uint32_t cut, bmax_bits, n_eval;
@@ -223,8 +225,12 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
 
   // ---- pass 1: statistics and tile codes
   float m_run[NB], z_run[NB];
+  const int n_segs = (L + a.seg_keys - 1) / a.seg_keys;  // at most kStreamMaxPerWg (the plan)
+  float2* const red_first = reinterpret_cast<float2*>(bins);
   stats_tiles<D, NB, NW, S>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run,
-                            TileCodes<NB>{codes_u, ub, c, l32, lane});
+                            TileCodes<NB>{codes_u, ub, c, l32, lane},
+                            n_segs > 1 ? red_first + wave * R : nullptr, NW * R,
+                            a.seg_keys / (NW * kTileKeys), n_segs);
   wait_vmem<0>();  // this wave's code stores have landed (other waves read them below)
   stats_to_lds<NB>(m_run, z_run, red + wave * R, l32, half);
   if (tid == 0) {
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   }
   __syncthreads();
   if (tid < R) {
-    const float2 v = merge_waves<NW, R>(red, tid);
+    const float2 v = merge_unit<NW, R>(red_first, NW * R, n_segs, red, tid);
     bsh[tid] = v.x + __builtin_log2f(v.y);  // b = M + log2 Z, base 2
     const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * 32 + tid;
     a.row_max_out[ri] = v.x * kLn2;
@@ -609,7 +615,7 @@ hipError_t launch_stream_window_cands(const Shape& s, const StreamPlan& plan, co
                                       uint64_t* cand_out, float* cand_max, int cand_stride,
                                       uint32_t* codes, bool sigma_all, const CandSelect* sel,
                                       hipStream_t stream) {
-  if (plan.max_segs != 1 || !cand_out || !cand_max || !codes || s.max_len > kCandMaxLen)
+  if (!plan.one_wg() || !cand_out || !cand_max || !codes || s.max_len > kCandMaxLen)
     return hipErrorInvalidValue;
   if (sel && (!sel->lambda2 || !sel->sel_idx || (sel->k_out && (!sel->v || !sel->v_out))))
     return hipErrorInvalidValue;

@@ -1,5 +1,6 @@
 // Both streaming passes over one whole unit in one workgroup (section 3.1, Eq. (1); section 3.2,
-// Eq. (3)), for launches in which every (problem, kv head) unit is a single segment.  The unit's
+// Eq. (3)), for launches in which one workgroup takes every (problem, kv head) unit (one segment, or
+// up to three whose statistics are kept apart and merged as if a workgroup each had formed them).  The unit's
 // row statistics are complete when its own pass 1 ends, so its pass 2 follows at once, with the
 // queries still in registers and the first key tiles of pass 2 loaded while the waves' statistics
 // are merged; no workgroup waits for any other.  The per-segment loops are in stream_passes.h.
@@ -20,7 +21,7 @@ __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a)
   constexpr int R = Gm::R, NS = Gm::NS;
   static_assert(OUT != kOutCand, "candidate mode: stream_prune.hip");
   __shared__ __align__(16) uint16_t ring[NW][S * Gm::TE];
-  __shared__ float2 red[NW][R];
+  __shared__ float2 red[kStreamMaxPerWg][NW][R];  // per segment of the unit
   __shared__ __align__(16) float bsh[R];
 
   const int g = blockIdx.y, p = blockIdx.z;
@@ -42,15 +43,19 @@ __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a)
   ks.prologue(my_tiles);
   hold_until_loaded<D, NB>(q);
 
+  const int n_segs = (L + a.seg_keys - 1) / a.seg_keys;  // at most kStreamMaxPerWg (the plan)
+  float2* const red_last = &red[n_segs - 1][0][0];
   float m_run[NB], z_run[NB];
-  stats_tiles<D, NB, NW, S, W>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run);
+  stats_tiles<D, NB, NW, S, W>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run, NoTileHook{},
+                               n_segs > 1 ? red[0][wave] : nullptr, NW * R,
+                               a.seg_keys / (NW * kTileKeys), n_segs);
   // every load of pass 1 has landed and been read (its last wait is vmcnt(0)): the ring takes the
   // first tiles of pass 2 while the statistics are merged
   ks.prologue(my_tiles);
-  stats_to_lds<NB>(m_run, z_run, red[wave], l32, half);
+  stats_to_lds<NB>(m_run, z_run, red_last + wave * R, l32, half);
   __syncthreads();
   if (threadIdx.x < R) {
-    const float2 v = merge_waves<NW, R>(&red[0][0], threadIdx.x);
+    const float2 v = merge_unit<NW, R>(&red[0][0][0], NW * R, n_segs, red_last, threadIdx.x);
     // b = M + log2 Z, base 2; +inf in the padding of the last block
     bsh[threadIdx.x] = W == 32 || threadIdx.x < G * W ? v.x + __builtin_log2f(v.y) : INFINITY;
   }
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(NW * 64, 1) void window_stream_kernel(StreamArgs a)
   wait_vmem<0>();  // no load into the ring may outlive the workgroup
   // the row statistics, merged again from the same entries in the same order
   if (threadIdx.x < (W == 32 ? R : G * W)) {
-    const float2 v = merge_waves<NW, R>(&red[0][0], threadIdx.x);
+    const float2 v = merge_unit<NW, R>(&red[0][0][0], NW * R, n_segs, red_last, threadIdx.x);
     const size_t ri = ((size_t)p * a.h_q + (size_t)g * G) * W + threadIdx.x;
     a.row_max_out[ri] = v.x * kLn2;
     a.row_sum_out[ri] = v.y;
@@ -93,7 +98,7 @@ template <int D, int NB, int W> struct WindowLaunch {
 hipError_t launch_stream_window(const Shape& s, const StreamPlan& plan, const void* q_win,
                                 const void* k, float scale, float* row_max, float* row_sum,
                                 float* mu, float* sigma, bool sigma_all, hipStream_t stream) {
-  if (plan.max_segs != 1) return hipErrorInvalidValue;  // a unit must be one segment
+  if (!plan.one_wg()) return hipErrorInvalidValue;
   stream::StreamArgs a = stream::base_args(s, plan, q_win, k, scale);
   a.row_max_out = row_max;
   a.row_sum_out = row_sum;
@@ -107,7 +112,7 @@ hipError_t launch_stream_window_scores(const Shape& s, const StreamPlan& plan, c
                                        const void* k, float scale, const float* lambda1,
                                        float w_mu, float* row_max, float* row_sum, float* score,
                                        bool sigma_all, hipStream_t stream) {
-  if (plan.max_segs != 1 || !score) return hipErrorInvalidValue;
+  if (!plan.one_wg() || !score) return hipErrorInvalidValue;
   stream::StreamArgs a = stream::base_args(s, plan, q_win, k, scale);
   a.row_max_out = row_max;
   a.row_sum_out = row_sum;

@@ -8,11 +8,14 @@ namespace stream {
 namespace {
 
 // ------------------------------------------------------------------------------------------------
-// Units split over several segments, one launch: every workgroup runs pass 1 over its segment,
-// publishes the segment's (m, z) per row and raises its unit's arrival counter, issues pass 2's
-// first tile loads, and waits (a bounded poll) until every segment of the unit has arrived; then it
-// merges the unit's partials into the normalisers and runs pass 2 over the same segment, with the
-// queries still in registers.  Nothing assumes that all workgroups are resident at once: a
+// Units split over several workgroups, one launch: every workgroup runs pass 1 over each of its
+// segments (per_wg consecutive ones), publishes the segments' (m, z) per row and adds them to its
+// unit's arrival counter, issues pass 2's first tile loads, and waits (a bounded poll) until every
+// segment of the unit has arrived; then it merges the unit's partials into the normalisers and runs
+// pass 2 over its keys, with the queries still in registers.  Segments stay the unit of the
+// statistics whatever per_wg is: 80 units of 30000 keys in four segments are 320 workgroups, over
+// the chip's CUs, so two segments each go to 160 (the eviction pass 421 -> 368 us, before with two
+// launches and mu, sigma in memory).  Nothing assumes that all workgroups are resident at once: a
 // workgroup whose poll runs out computes the partials of the unit's other segments itself (the
 // same code over the same keys, hence the same values, written to the same slots) and goes on,
 // so a launch that shares the chip with other work is slower, never wrong or stuck.
@@ -39,12 +42,13 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
   __shared__ __align__(16) float bsh[R];
   __shared__ uint32_t all_arrived;
 
-  const int seg = blockIdx.x, g = blockIdx.y, p = blockIdx.z;
+  const int seg = blockIdx.x * a.per_wg, g = blockIdx.y, p = blockIdx.z;  // its first segment
   const int L = a.lens[p];
-  const int k0 = seg * a.seg_keys;
-  if (k0 >= L) return;  // not one of this unit's segments (it never counts as one)
-  const int k1 = min(k0 + a.seg_keys, L);
+  if ((int64_t)seg * a.seg_keys >= L) return;  // none of this unit's segments
   const int n_seg = (L + a.seg_keys - 1) / a.seg_keys;
+  const int seg_end = min(seg + a.per_wg, n_seg);  // one past its last
+  const int k0 = seg * a.seg_keys;
+  const int k1 = (int)min((int64_t)seg_end * a.seg_keys, (int64_t)L);
   const int G = a.h_q / a.h_kv;
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -61,28 +65,42 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
 
   KeyStream<D, NB, NW, S> ks{ring[wave], kg, k0, k1, wave, lane};
   const int my_tiles = tiles_of(k0, k1);
+  // the key stream of segment sg alone and the wave's tiles in it
+  auto stream_of = [&](int sg) {
+    const int s0 = sg * a.seg_keys;
+    return KeyStream<D, NB, NW, S>{ring[wave], kg, s0, (int)min((int64_t)s0 + a.seg_keys, (int64_t)L), wave, lane};
+  };
 
   bf16x8_t q[NB][NS];
   load_queries<D, NB, W>(q, a.q_win + ((size_t)p * a.h_q + (size_t)g * G) * W * D, l32, half, G * W);
-  ks.prologue(my_tiles);
+  {
+    const auto st = stream_of(seg);
+    st.prologue(tiles_of(st.k0, st.k1));
+  }
   hold_until_loaded<D, NB>(q);
 
-  // pass 1 over segment `sg` (keys [s0, s1)) by the whole workgroup; its partial goes to its slot
-  // with device-coherent stores, complete before the workgroup leaves the final barrier
-  auto pass1 = [&](const KeyStream<D, NB, NW, S>& st, int sg, int s1, int n_my) {
+  // pass 1 over segment `sg`, whose first tiles are loading, by the whole workgroup; its partial
+  // goes to its slot with device-coherent stores, complete before the workgroup leaves the final
+  // barrier.  The first tiles of segment `next` (none: negative) load meanwhile.
+  auto pass1 = [&](int sg, int next) {
+    const auto st = stream_of(sg);
     float m_run[NB], z_run[NB];
-    stats_tiles<D, NB, NW, S, W>(st, q, n_my, s1, L, c, l32, half, m_run, z_run);
+    stats_tiles<D, NB, NW, S, W>(st, q, tiles_of(st.k0, st.k1), st.k1, L, c, l32, half, m_run, z_run);
+    if (next >= 0) {
+      const auto sn = stream_of(next);
+      sn.prologue(tiles_of(sn.k0, sn.k1));
+    }
     stats_to_lds<NB>(m_run, z_run, red[wave], l32, half);
     __syncthreads();
     if (threadIdx.x < R) store_partial(part_u + (size_t)sg * R + threadIdx.x, merge_waves<NW, R>(&red[0][0], threadIdx.x));
     wait_vmem<0>();
     __syncthreads();  // red is free again, every partial store has completed
   };
-  pass1(ks, seg, k1, my_tiles);
+  for (int sg = seg; sg < seg_end; ++sg) pass1(sg, sg + 1 < seg_end ? sg + 1 : -1);
   // The partials and the counter are device-coherent atomics (no cache-wide write-back or
   // invalidation, which would disturb every workgroup streaming keys through the same L2).
   if (threadIdx.x == 0)
-    __hip_atomic_fetch_add(arrive + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(arrive + unit, (uint32_t)(seg_end - seg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // the ring is free (pass 1's last wait covered all its loads): pass 2's first tiles load while
   // the other segments arrive
   ks.prologue(my_tiles);
@@ -100,12 +118,10 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
     // Not every segment arrived in time: the other segments' partials are computed here.
     wait_vmem<0>();  // pass 2's prologue loads own the ring until they land
     for (int sg = 0; sg < n_seg; ++sg) {
-      if (sg == seg) continue;
-      const int s0 = sg * a.seg_keys, s1 = min(s0 + a.seg_keys, L);
-      KeyStream<D, NB, NW, S> other{ring[wave], kg, s0, s1, wave, lane};
-      const int n_my = tiles_of(s0, s1);
-      other.prologue(n_my);
-      pass1(other, sg, s1, n_my);
+      if (sg >= seg && sg < seg_end) continue;
+      const auto st = stream_of(sg);
+      st.prologue(tiles_of(st.k0, st.k1));
+      pass1(sg, -1);
     }
     ks.prologue(my_tiles);
   }
@@ -165,7 +181,7 @@ template <int D, int NB, int W> struct CoopLaunch {
     return reinterpret_cast<const void*>(window_coop_kernel<D, NB, W, ALL, kWaves, 2, SC>);
   }
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st, uint32_t* arrive,
-                        uint32_t spin_limit, bool* launched) {
+                        uint32_t spin_limit, int64_t n_wgs, bool* launched) {
     const bool sc = args.score != nullptr;
     const void* kern = args.sigma_all ? (sc ? kernel<true, true>() : kernel<true, false>())
                                       : (sc ? kernel<false, true>() : kernel<false, false>());
@@ -174,8 +190,8 @@ template <int D, int NB, int W> struct CoopLaunch {
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kThreads, 0);
     if (e != hipSuccess) return e;
-    const dim3 grid(args.max_segs, s.h_kv, s.n_prob);
-    if ((int64_t)grid.x * grid.y * grid.z > (int64_t)per_cu * n_cu) {
+    const dim3 grid((args.max_segs + args.per_wg - 1) / args.per_wg, s.h_kv, s.n_prob);
+    if (n_wgs > (int64_t)per_cu * n_cu) {  // (the grid's other workgroups leave at once)
       *launched = false;
       return hipSuccess;
     }
@@ -216,7 +232,8 @@ hipError_t launch_stream_window_coop(const Shape& s, const StreamPlan& plan, con
     a.w_mu = sm->w_mu;
   }
   uint32_t* arrive = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_counter_offset(s, plan));
-  return stream::launch_for_shape<stream::CoopLaunch>(s, a, stream, arrive, spin_limit, launched);
+  return stream::launch_for_shape<stream::CoopLaunch>(s, a, stream, arrive, spin_limit,
+                                                        plan.n_wgs, launched);
 }
 
 }  // namespace kv

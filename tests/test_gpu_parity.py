@@ -23,6 +23,11 @@ def _all(run, heads=None, certified=False):
     return reports
 
 
+def _all_of(run, js):
+    """Compare problems js of a run (None: all)."""
+    print("  ", gpu_cases.summarize(gpu_cases.check_all(run, js=js)), flush=True)
+
+
 def test_tiny_f32_unfused_with_attention():
     """fp32 path, 2 query heads on 1 kv head, d=64, W=8 (general window reduction); certified."""
     _all(gpu_cases.run_case("tiny_f32", want_attn=True), certified=True)
@@ -358,7 +363,7 @@ def test_short_windows(h_q, h_kv, d, w, lens, n_layers, monkeypatch):
     for sigma_rows in ("group_mean", "all_rows"):
         monkeypatch.delenv("KVEVICT_SPIN_LIMIT", raising=False)
         run = gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows)
-        print("  ", gpu_cases.summarize(gpu_cases.check_all(run, js=probs)), flush=True)
+        _all_of(run, probs)
         if n_layers > 2:
             continue
         monkeypatch.setenv("KVEVICT_SPIN_LIMIT", "0")
@@ -377,6 +382,26 @@ def test_segments_merged_by_the_second_launch():
     n_seg = -(-int(wl.lens.max()) // seg)
     assert n_seg == 2 and n_seg * wl.n_prob * wl.h_kv > 256
     _all(gpu_cases.run_gpu(wl, fused=True))
+
+
+@pytest.mark.parametrize("n_seq,n_layers,lens,h_q,d,exact", [
+    (1, 24, [5000], 32, 128, True), (1, 24, [1500], 16, 64, True), (1, 14, [9000], 32, 128, True), (1, 10, [9000], 32, 128, True),
+    (1, 10, [9000], 8, 64, True), (2, 16, [2500, 700], 32, 128, True),
+    (38, 1, [300] * 37 + [6000], 8, 128, False)])
+def test_workgroups_of_several_segments(n_seq, n_layers, lens, h_q, d, exact):
+    """Batches whose segments do not fit the chip at once: 192 units of two segments and
+    112 of three in one workgroup each (also with no tile of the last for some waves), 80 units of four segments in
+    two workgroups, ragged units of one and two, and 304 units of up to six, which take two
+    launches.  The statistics are merged segment by segment whatever the workgroups, so the row
+    statistics equal those of kv_window_scores (one workgroup per segment, merged by its combine
+    kernel in segment order, which for up to four segments is the same order) bit for bit."""
+    wl = _shape_workload(h_q, 8, d, n_seq, n_layers, lens, budget=32)
+    run = gpu_cases.run_gpu(wl, timed=True)
+    _all_of(run, [0, wl.n_prob - 1])
+    if exact:
+        plain = gpu_cases.run_gpu(wl, fused=False)
+        for name in ("row_max", "row_sum"):
+            assert np.array_equal(run.host[name].view(np.uint32), plain.host[name].view(np.uint32)), name
 
 
 @pytest.mark.parametrize("h_q,h_kv,d", STREAM_SHAPES)
