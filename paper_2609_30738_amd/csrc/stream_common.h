@@ -83,6 +83,7 @@ struct StreamArgs {
   // candidate mode, pass 1: per unit code_stride words of tile codes (32 words per tile)
   uint32_t* codes;
   int code_stride;
+  int prune;  // pass 2 revisits only the tiles whose bound reaches the cut (else every tile)
   // candidate mode with the selection in the same launch (sel_idx != nullptr, every C_p <= 256):
   // the greedy's outputs as from the selection kernel, [n_prob][h_kv][budget], and with k_out the
   // compacted rows of K and V, [n_prob][h_kv][out_rows][D]

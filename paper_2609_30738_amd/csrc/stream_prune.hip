@@ -169,7 +169,10 @@ __device__ __forceinline__ void find_cut_bin(const uint32_t* hist, uint32_t top,
   }
 }
 
-template <int D, int NB, bool ALL, int NW, int S, bool SEL>
+// With PRUNE = false (units whose tiles hardly outnumber the candidates, so that almost every tile
+// would be revisited) pass 1 writes no codes, nothing is bounded or ordered, and pass 2 evaluates
+// every tile in its own order, as kv_window_base_scores does; the rest is the same.
+template <int D, int NB, bool ALL, int NW, int S, bool SEL, bool PRUNE>
 __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) {
   using Gm = SGeo<D, NB>;
   constexpr int R = Gm::R, NS = Gm::NS, NT = NW * 64;
@@ -227,11 +230,15 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   float m_run[NB], z_run[NB];
   const int n_segs = (L + a.seg_keys - 1) / a.seg_keys;  // at most kStreamMaxPerWg (the plan)
   float2* const red_first = reinterpret_cast<float2*>(bins);
-  stats_tiles<D, NB, NW, S>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run,
-                            TileCodes<NB>{codes_u, ub, c, l32, lane},
+  using Hook = std::conditional_t<PRUNE, TileCodes<NB>, NoTileHook>;
+  Hook hook;
+  if constexpr (PRUNE) hook = Hook{codes_u, ub, c, l32, lane};
+  stats_tiles<D, NB, NW, S>(ks, q, my_tiles, L, L, c, l32, half, m_run, z_run, hook,
                             n_segs > 1 ? red_first + wave * R : nullptr, NW * R,
                             a.seg_keys / (NW * kTileKeys), n_segs);
-  wait_vmem<0>();  // this wave's code stores have landed (other waves read them below)
+  const int n_cand = L - a.keep_tail;
+  if constexpr (PRUNE) wait_vmem<0>();  // the wave's code stores have landed (others read them below)
+  else ks.prologue(my_tiles);           // pass 2's first tiles load while the statistics are merged
   stats_to_lds<NB>(m_run, z_run, red + wave * R, l32, half);
   if (tid == 0) {
     cut = 0u;
@@ -247,12 +254,18 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   }
   __syncthreads();  // the normalisers are complete; red is free
 
+  for (int i = tid; i < kPruneBins; i += NT) red_hist[i] = 0u;
+  float* score_u = reinterpret_cast<float*>(codes_u);  // a tile's codes are dead once bounded
+  const ScoreOut so{score_u, lam1, a.w_mu};
+  const int bp = a.budgets ? a.budgets[p] : a.budget;
+  const int C = min(a.cand_mult * bp, n_cand);
+  int n_ord;   // tiles in the order of pass 2
+  float smax;  // the lane's largest evaluated score
+  if constexpr (PRUNE) {
   // ---- bounds of the thread's tiles tid + u NT (-inf: no candidate key, never revisited)
   uint32_t* cnt = bins;                  // [kOrderBins] tiles per bin
   uint32_t* off = bins + kOrderBins;     // [kOrderBins] first position of each bin, then a cursor
-  for (int i = tid; i < kPruneBins; i += NT) red_hist[i] = 0u;
   for (int i = tid; i < kOrderBins; i += NT) cnt[i] = 0u;
-  const int n_cand = L - a.keep_tail;
   const float wmu_p = fmaxf(a.w_mu, 0.f), lam1_p = fmaxf(lam1, 0.f);
   float bnd[kTilesPerThread];
   float lmax = 0.f;  // largest finite bound (bounds are positive)
@@ -327,29 +340,28 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   __syncthreads();  // the order is complete; the ring is free
 
   // ---- pass 2: exact scores of the wanted tiles, stored over their codes
-  const int n_ord = (int)n_eval;
-  const int bp = a.budgets ? a.budgets[p] : a.budget;
-  const int C = min(a.cand_mult * bp, n_cand);
+  n_ord = (int)n_eval;
   const int my_tiles2 = n_ord > wave ? (n_ord - wave + NW - 1) / NW : 0;
   // the second visit keeps its tiles in the caches: the selection reads the candidates' rows next
   KeyStream<D, NB, NW, S> ks2{ring + wave * S * Gm::TE, kg, 0, L, wave, lane, order, true};
   ks2.prologue(my_tiles2);
-  float* score_u = reinterpret_cast<float*>(codes_u);  // a tile's codes are dead once bounded
   // the cut's scan starts at the bin of the largest finite bound: scores above it (in tiles with a
   // masked key) are left out of the scan, which only lowers the cut
   const int scan_top = bmax > 0.f ? (int)(order_key(bmax) >> kPruneShift) : kPruneBins - 1;
   Prune pr{ub, red_hist, &cut, score_u, scan_top, n_cand, C, -INFINITY, 0};
-  const ScoreOut so{nullptr, lam1, a.w_mu};
   mu_sigma_tiles<D, NB, ALL, NW, S, kOutCand>(ks2, q, bsh, my_tiles2, L, L, c, inv_g, nullptr,
                                               nullptr, l32, half, so, &pr);
-  wait_vmem<0>();  // the score stores have landed; no load into the ring outlives the workgroup
-  float m = pr.smax;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if (lane == 0) {
-    c_max[wave] = m;
-    ev[wave] = (uint32_t)pr.evaluated;
+  smax = pr.smax;
+  if (lane == 0) ev[wave] = (uint32_t)pr.evaluated;
+  } else {
+    n_ord = (n_cand + kTileKeys - 1) / kTileKeys;  // the tiles with candidates, in their own order
+    for (int i = tid; i < n_ord; i += NT) order[i] = (uint16_t)i;
+    if (lane == 0) ev[wave] = (uint32_t)my_tiles;
+    mu_sigma_tiles<D, NB, ALL, NW, S, kOutScore>(ks, q, bsh, my_tiles, L, L, c, inv_g, nullptr,
+                                                 nullptr, l32, half, so);
+    smax = -INFINITY;
   }
+  wait_vmem<0>();  // the score stores have landed; no load into the ring outlives the workgroup
 
   // ---- the unit's candidates: the C largest entries (order key of the score, position) among
   //      the evaluated keys, written in ascending position order.  The C-th largest entry is
@@ -365,19 +377,48 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   // [order position][key in tile] by waves 1.. while wave 0 finds the first digit of the cut; the
   // passes below visit them there
   uint32_t* okc = reinterpret_cast<uint32_t*>(ring);
+  // device-coherent load: the line may still sit in this CU's vector cache with the tile's codes,
+  // read before the score was stored over them
+  auto load_score = [&](int key) __attribute__((always_inline)) {
+    return __uint_as_float(__hip_atomic_load(reinterpret_cast<uint32_t*>(score_u + key),
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  };
+  if constexpr (!PRUNE) {
+    // the scores of every candidate key: copied, counted and their maximum taken by all waves, four
+    // loads of a thread in flight
+    for (int i0 = tid; i0 < n_ord * kTileKeys; i0 += 4 * NT) {
+      float sv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sv[u] = i0 + u * NT < n_cand ? load_score(i0 + u * NT) : 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u * NT;
+        const bool in = i < n_cand;
+        const uint32_t ok = order_key(sv[u]);
+        if (in) {
+          smax = fmaxf(smax, sv[u]);
+          okc[i] = ok;
+        }
+        wave_hist_add(red_hist, ok >> kPruneShift, in);
+      }
+    }
+  }
+  {
+    float m = smax;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if (lane == 0) c_max[wave] = m;
+  }
+  if constexpr (!PRUNE) __syncthreads();  // the histogram is complete
   if (wave == 0) {
     find_cut_bin(red_hist, kPruneBins - 1, C, lane, &cut, &bmax_bits);
-  } else {
+  } else if constexpr (PRUNE) {
     constexpr int kVisit = (NT - 64) / kTileKeys;  // tiles per visit
     for (int p0 = 0; p0 < n_pos; p0 += kVisit) {
       const int pos = p0 + (tid - 64) / kTileKeys;
       if (pos < n_pos && (pos / NW) < (int)ev[pos % NW]) {
         const int key = (int)order[pos] * kTileKeys + (tid % kTileKeys);
-        // device-coherent load: the line may still sit in this CU's vector cache with the tile's
-        // codes, read before the score was stored over them
-        if (key < n_cand)
-          okc[pos * kTileKeys + tid % kTileKeys] = order_key(__uint_as_float(__hip_atomic_load(
-              reinterpret_cast<uint32_t*>(score_u + key), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+        if (key < n_cand) okc[pos * kTileKeys + tid % kTileKeys] = order_key(load_score(key));
       }
     }
   }
@@ -590,13 +631,16 @@ template <int D, int NB, int W> struct PruneLaunch {
   }
   static hipError_t run32(const Shape& s, const StreamArgs& args, hipStream_t st) {
     const dim3 grid(1, s.h_kv, s.n_prob);
-    if (args.sel_idx) {
-      if (args.sigma_all) window_prune_kernel<D, NB, true, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args);
-      else window_prune_kernel<D, NB, false, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args);
-    } else {
-      if (args.sigma_all) window_prune_kernel<D, NB, true, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args);
-      else window_prune_kernel<D, NB, false, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args);
-    }
+    const bool all = args.sigma_all != 0, prune = args.prune != 0;
+    auto launch = [&](auto al, auto pr) {
+      constexpr bool A = decltype(al)::value, P = decltype(pr)::value;
+      if (args.sel_idx) window_prune_kernel<D, NB, A, kWaves, 2, true, P><<<grid, kThreads, 0, st>>>(args);
+      else window_prune_kernel<D, NB, A, kWaves, 2, false, P><<<grid, kThreads, 0, st>>>(args);
+    };
+    if (all && prune) launch(std::true_type{}, std::true_type{});
+    else if (all) launch(std::true_type{}, std::false_type{});
+    else if (prune) launch(std::false_type{}, std::true_type{});
+    else launch(std::false_type{}, std::false_type{});
     return hipGetLastError();
   }
 };
@@ -634,6 +678,12 @@ hipError_t launch_stream_window_cands(const Shape& s, const StreamPlan& plan, co
   a.keep_tail = keep_tail;
   a.codes = codes;
   a.code_stride = cand_code_stride(s);
+  // Bounds pay where tiles outnumber candidates: at most as many tiles as candidates, and a cut
+  // that is not confined to few clusters has one in almost every tile (256 units of 8000 keys,
+  // C = 256: 287 us with bounds, 267 without; of 2000 keys 129 and 117).  Above, few tiles may
+  // suffice (16000 keys, C = 256: 257 and 442; 8000 keys, C = 128: 139 and 232), or not (10000
+  // keys, C = 256, in flat scores: 346 and 317).
+  a.prune = s.max_len / stream::kTileKeys > cand_stride ? 1 : 0;
   if (sel) {
     a.lambda2 = sel->lambda2;
     a.sel_idx = sel->sel_idx;
