@@ -184,7 +184,10 @@ __device__ __forceinline__ void cosines(const uint16_t* __restrict__ kg, const i
   __syncthreads();
 }
 
-// The greedy of one wave over the triangle: bp steps (bp <= C), each admitting the slot of largest
+// The greedy of one wave over the triangle (bound by the latency of a step: the scores' fused
+// multiply-add, six DPP maxima, the ballots' minimum, the triangle's address and its LDS read; 0.206
+// us per step, 0.281 when the winner's slot group was found by branches, the addresses went through
+// vector registers and the bookkeeping came before the read): bp steps (bp <= C), each admitting the slot of largest
 // fmaf(lam2, corr, s~) (ties to the lower slot), corr being a slot's largest cosine to the slots
 // admitted before (0 before the first).
 struct Greedy {
@@ -214,6 +217,27 @@ struct Greedy {
 #pragma unroll
     for (int q = 0; q < kSlots; ++q) gv[q] = tri[cq[q] <= s ? offq[q] + s : off_s + cq[q]];
   }
+  // The lowest slot of the ballots of the four slot groups, at most `limit`, in scalar registers
+  // (left to the compiler the minimum goes through vector registers, with wait states both ways).
+  __device__ __forceinline__ static uint32_t lowest_slot(uint64_t m0, uint64_t m1, uint64_t m2,
+                                                         uint64_t m3, uint32_t limit) {
+    uint32_t s, a, b, c;
+    asm("s_ff1_i32_b64 %0, %4\n\t"
+        "s_ff1_i32_b64 %1, %5\n\t"
+        "s_ff1_i32_b64 %2, %6\n\t"
+        "s_ff1_i32_b64 %3, %7\n\t"  // ~0 for an empty ballot
+        "s_or_b32 %1, %1, 64\n\t"
+        "s_or_b32 %2, %2, 0x80\n\t"
+        "s_or_b32 %3, %3, 0xc0\n\t"
+        "s_min_u32 %0, %0, %1\n\t"
+        "s_min_u32 %2, %2, %3\n\t"
+        "s_min_u32 %0, %0, %8\n\t"
+        "s_min_u32 %0, %0, %2"
+        : "=&s"(s), "=&s"(a), "=&s"(b), "=&s"(c)
+        : "s"(m0), "s"(m1), "s"(m2), "s"(m3), "s"(limit)
+        : "scc");
+    return s;
+  }
   // Steps t = 0 .. bp - 1: trace_slot[t] = the admitted slot, and with KEYS trace_key[t] = the
   // order key of its score (the wave's largest score; -inf's key when no live slot is left, in
   // which case slot C - 1 is recorded).  A step: the largest score of the wave, then the lowest
@@ -226,49 +250,37 @@ struct Greedy {
   __device__ __forceinline__ void run(const float* tri, int C, int bp, float lam2, int lane,
                                       uint32_t* trace_slot, uint32_t* trace_key) {
     float gv[kSlots];
-    for (int t = 0; t < bp; ++t) {
-      if (t > 0) {
 #pragma unroll
-        for (int q = 0; q < kSlots; ++q) corr[q] = __builtin_elementwise_maximum(corr[q], gv[q]);
-      }
+    for (int q = 0; q < kSlots; ++q) gv[q] = 0.f;  // corr starts at 0
+    for (int t = 0; t < bp; ++t) {
       float sc[kSlots];
 #pragma unroll
-      for (int q = 0; q < kSlots; ++q) sc[q] = fmaf(lam2, corr[q], st[q]);
+      for (int q = 0; q < kSlots; ++q) {
+        corr[q] = __builtin_elementwise_maximum(corr[q], gv[q]);
+        sc[q] = fmaf(lam2, corr[q], st[q]);
+      }
       static_assert(kSlots == 4, "four slot groups");
       const float lm = __builtin_elementwise_maximum(__builtin_elementwise_maximum(sc[0], sc[1]),
                                                      __builtin_elementwise_maximum(sc[2], sc[3]));
       const float wm = wave_max_uniform(lm);
       int slot = C - 1;  // no live slot left (every score -inf or NaN)
       if (!CHECK || wm > -INFINITY) {
-        uint64_t m = __ballot(sc[0] == wm);
-        int q = 0;
-#pragma unroll
-        for (int u = 1; u < kSlots; ++u) {
-          if (m == 0) {
-            m = __ballot(sc[u] == wm);
-            q = u;
-          }
-        }
-        slot = 64 * q + (__ffsll((unsigned long long)m) - 1);
+        slot = (int)lowest_slot(__ballot(sc[0] == wm), __ballot(sc[1] == wm), __ballot(sc[2] == wm),
+                                __ballot(sc[3] == wm), (uint32_t)(C - 1));
       }
-      last = __builtin_amdgcn_readfirstlane(slot);
-      // the step's record (every lane stores the same value)
+      last = slot;
+      // the cosines of every slot to it for the next step: a slot before it reads its own row's
+      // entry (byte address + 4 row_off(slot)), one after it the admitted slot's (+ 4 slot)
+      const char* col = reinterpret_cast<const char*>(tri + last);
+      const char* row = reinterpret_cast<const char*>(tri - 1) + 2 * last * (2 * C - 3 - last);
+#pragma unroll
+      for (int q = 0; q < kSlots; ++q)
+        gv[q] = *reinterpret_cast<const float*>(lane + 64 * q <= last ? col + off4[q] : row + cq4[q]);
+      // the step's record (every lane stores the same value); slot `last` leaves the race
       trace_slot[t] = (uint32_t)last;
       if constexpr (KEYS) trace_key[t] = wm_key(wm, sc);
-      // slot `last` leaves the race; the cosines of every slot to it for the next step
-      const int ql = last >> 6, ll = last & 63;
 #pragma unroll
-      for (int q = 0; q < kSlots; ++q) st[q] = q == ql && lane == ll ? -INFINITY : st[q];
-      if (t + 1 < bp) {
-        // byte addresses: its column (slot < last) at + 4 row_off(slot), its row at + 4 slot
-        const char* col = reinterpret_cast<const char*>(tri + last);
-        const char* row = reinterpret_cast<const char*>(tri + row_off(last, C));
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-          const bool in_col = q < ql || (q == ql && lane <= ll);
-          gv[q] = *reinterpret_cast<const float*>(in_col ? col + off4[q] : row + cq4[q]);
-        }
-      }
+      for (int q = 0; q < kSlots; ++q) st[q] = lane + 64 * q == last ? -INFINITY : st[q];
     }
   }
   // run<KEYS, CHECK> with CHECK decided by lam2
