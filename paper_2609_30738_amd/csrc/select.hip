@@ -1,7 +1,7 @@
 // Greedy diversity-aware admission (section 3.2, Eq. (2), (4), (5)) on gfx950.
 //
-// One workgroup per (problem, kv head): 1024 threads for bf16 keys (one candidate per thread), 256
-// for fp32 keys (up to four per thread, whose key rows need more registers):
+// One workgroup per (problem, kv head): 1024 threads for bf16 keys, 256 for fp32 keys (whose rows
+// need more registers), 512 and 256 for a quad greedy that starts from a candidate list:
 //   1. base scores s_i = fma(lambda1, sigma_i, w_mu mu_i) over the candidates [0, n_cand) (optionally
 //      max-pooled over an odd window of positions, the outside of [0, n_cand) ignored), their maximum
 //      (the normaliser, clamped at 1e-12), and the C-th largest score by a most-significant-digit
@@ -17,11 +17,11 @@
 //        in LDS; then ONE wave runs every step, each lane holding up to four candidates' s~ and
 //        running max-cosine: a step reads one triangle entry per candidate against the last
 //        admitted slot and takes a DPP / permlane maximum, with no barrier;
-//      - rows (larger C): thread t owns candidates t, t + NT, ... and keeps their keys in
-//        registers; each step updates the running maxima against the last admitted key (read from
-//        an LDS copy of the candidate keys), forms s~ + lambda2 * corr, and finds the (score,
-//        lowest slot) maximum: a DPP / permlane maximum and a ballot inside each wave, then one
-//        barrier; the per-wave winners are double-buffered so that one barrier per step suffices.
+//      - quad (larger C, fp32 keys; select_quad.h): every four lanes share four candidates' keys in
+//        registers; each step updates the running maxima against the last admitted key, forms
+//        s~ + lambda2 * corr, and finds the (score, lowest slot) maximum: a DPP maximum and a ballot
+//        inside each wave, then one barrier; the waves' records are double-buffered so that one
+//        barrier per step suffices.
 #include <float.h>
 
 #include <algorithm>
@@ -30,6 +30,7 @@
 #include "compact_rows.h"
 #include "kernels.h"
 #include "select_gram.h"
+#include "select_quad.h"
 
 namespace kv {
 
@@ -39,20 +40,14 @@ constexpr int kMaxCandBytes = 131072;        // LDS copy of the candidate keys
 constexpr int kMaxStagedKeyBytes = 139264;  // LDS copy of every candidate's score key (34816)
 constexpr size_t kLdsBytes = 163840;        // LDS of one CU
 constexpr int kMaxSlotWords = 64;           // bitmap words over the candidate slots (C <= 2048)
+// How the greedy forms its cosines: one triangle of all pairs (select_gram.h), or against the last
+// admitted row in every step (select_quad.h), the rows of all candidates in LDS or only the waves'
+// best ones.
+enum SelectMode { kGram = 0, kQuadRows = 1, kQuadBest = 2 };
+// threads of the quad greedy: with four candidates per quad 64 registers of chains at bf16 and
+// d = 128, 128 at fp32
+constexpr int quad_threads(int dt) { return dt == kDtBf16 ? 512 : 256; }
 
-// (score, slot) packed so that a larger value means a larger score, then a lower slot.
-__device__ __forceinline__ uint64_t pack_best(float score, int slot) {
-  return ((uint64_t)order_key(score) << 32) | (uint32_t)(0x7FFFFFFF - slot);
-}
-__device__ __forceinline__ int unpack_slot(uint64_t v) { return 0x7FFFFFFF - (int)(uint32_t)v; }
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint64_t o = __shfl_xor(v, off, 64);
-    v = o > v ? o : v;
-  }
-  return v;
-}
 // Maximum over the 64 lanes, in every lane: quad and row steps with DPP, then permlane swaps
 // between rows and between the wave's halves.
 __device__ __forceinline__ float wave_max_f(float v) {
@@ -70,116 +65,11 @@ __device__ __forceinline__ float wave_max_f(float v) {
 #undef KV_DPPF
 }
 
-// (score, slot) of the best candidate of the wave, ties to the lowest slot.  With one candidate
-// per lane (slots ascending with the lane) the lowest tied lane holds the lowest slot.
-template <bool ONE_PER_LANE>
-__device__ __forceinline__ uint64_t wave_best(float score, int slot) {
-  const float wm = wave_max_f(score);
-  const uint64_t tied = __ballot(score == wm);
-  int best = __builtin_amdgcn_readlane(slot, __ffsll((unsigned long long)tied) - 1);
-  if (!ONE_PER_LANE && wm > -INFINITY && __popcll(tied) > 1) {
-    // exact tie between lanes: lowest slot among them (a wave with no live slot left ties at -inf)
-    uint64_t rest = tied;
-    while (rest) {
-      const int l = __ffsll((unsigned long long)rest) - 1;
-      best = min(best, __builtin_amdgcn_readlane(slot, l));
-      rest &= rest - 1;
-    }
-  }
-  return pack_best(wm, best);
-}
-
-// Key row of one candidate held in registers, and its dot product with a row in LDS.
-template <int DT, int D> struct KeyRow;
-
-template <int D> struct KeyRow<kDtBf16, D> {
-  typedef __bf16 __attribute__((ext_vector_type(2))) bf2;
-  bf2 v[D / 2];
-  __device__ __forceinline__ void load(const uint16_t* row) {
-    const uint4* src = reinterpret_cast<const uint4*>(row);
-#pragma unroll
-    for (int q = 0; q < D / 8; ++q) {
-      const uint4 x = src[q];
-      v[4 * q + 0] = __builtin_bit_cast(bf2, x.x);
-      v[4 * q + 1] = __builtin_bit_cast(bf2, x.y);
-      v[4 * q + 2] = __builtin_bit_cast(bf2, x.z);
-      v[4 * q + 3] = __builtin_bit_cast(bf2, x.w);
-    }
-  }
-  __device__ __forceinline__ void store(uint16_t* row) const {
-    uint4* dst = reinterpret_cast<uint4*>(row);
-#pragma unroll
-    for (int q = 0; q < D / 8; ++q)
-      dst[q] = make_uint4(__builtin_bit_cast(uint32_t, v[4 * q + 0]), __builtin_bit_cast(uint32_t, v[4 * q + 1]),
-                          __builtin_bit_cast(uint32_t, v[4 * q + 2]), __builtin_bit_cast(uint32_t, v[4 * q + 3]));
-  }
-  __device__ __forceinline__ float dot_lds(const uint16_t* row) const {
-    const uint4* src = reinterpret_cast<const uint4*>(row);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < D / 8; ++q) {
-      const uint4 x = src[q];
-      acc[0] = __builtin_amdgcn_fdot2_f32_bf16(v[4 * q + 0], __builtin_bit_cast(bf2, x.x), acc[0], false);
-      acc[1] = __builtin_amdgcn_fdot2_f32_bf16(v[4 * q + 1], __builtin_bit_cast(bf2, x.y), acc[1], false);
-      acc[2] = __builtin_amdgcn_fdot2_f32_bf16(v[4 * q + 2], __builtin_bit_cast(bf2, x.z), acc[2], false);
-      acc[3] = __builtin_amdgcn_fdot2_f32_bf16(v[4 * q + 3], __builtin_bit_cast(bf2, x.w), acc[3], false);
-    }
-    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  }
-  __device__ __forceinline__ float sq_norm() const {
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < D / 2; ++i)
-      acc[i & 3] = __builtin_amdgcn_fdot2_f32_bf16(v[i], v[i], acc[i & 3], false);
-    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  }
-};
-
-template <int D> struct KeyRow<kDtF32, D> {
-  float v[D];
-  __device__ __forceinline__ void load(const float* row) {
-    const float4* src = reinterpret_cast<const float4*>(row);
-#pragma unroll
-    for (int q = 0; q < D / 4; ++q) {
-      const float4 x = src[q];
-      v[4 * q + 0] = x.x;
-      v[4 * q + 1] = x.y;
-      v[4 * q + 2] = x.z;
-      v[4 * q + 3] = x.w;
-    }
-  }
-  __device__ __forceinline__ void store(float* row) const {
-    float4* dst = reinterpret_cast<float4*>(row);
-#pragma unroll
-    for (int q = 0; q < D / 4; ++q) dst[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-  }
-  __device__ __forceinline__ float dot_lds(const float* row) const {
-    const float4* src = reinterpret_cast<const float4*>(row);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < D / 4; ++q) {
-      const float4 x = src[q];
-      acc[0] = fmaf(v[4 * q + 0], x.x, acc[0]);
-      acc[1] = fmaf(v[4 * q + 1], x.y, acc[1]);
-      acc[2] = fmaf(v[4 * q + 2], x.z, acc[2]);
-      acc[3] = fmaf(v[4 * q + 3], x.w, acc[3]);
-    }
-    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  }
-  __device__ __forceinline__ float sq_norm() const {
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc[i & 3] = fmaf(v[i], v[i], acc[i & 3]);
-    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  }
-};
-
 template <int NW> struct SelectShared {
   uint32_t hist[NW][256];
   uint32_t scan[256];
   uint32_t wave_cnt[2][NW];
   float wave_max[NW];
-  uint4 best[2][NW];  // per wave and step parity: the packed (score, slot) pair, 1 / |k|
   uint32_t halo[2][32];  // raw keys left of a pooling chunk (pool_h <= 31)
   uint32_t sel_threshold;
   int sel_need;
@@ -357,8 +247,8 @@ struct CompactOut {
 
 }  // namespace
 
-template <int DT, int D, int NT, int CPT, bool STAGED, bool GRAM>
-__global__ __launch_bounds__(NT) void mmr_select_kernel(
+template <int DT, int D, int NT, int J, bool STAGED, int MODE>
+__global__ __launch_bounds__(NT, NT >= 512 ? 4 : 2) void mmr_select_kernel(
     const float* __restrict__ mu, const float* __restrict__ sigma,
     const float* __restrict__ score, const uint64_t* __restrict__ cand_in,
     const float* __restrict__ cand_in_max, uint64_t* __restrict__ cut_out,
@@ -375,7 +265,7 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
   __shared__ SelectShared<kWaves> sh;
   // dynamic LDS: [max_cand] positions, [max_cand] 1/|k|, [max_cand] s~ (Gram greedy), then a region
   // that first holds the order-preserving keys of every candidate score (STAGED) and then the
-  // candidates' key rows or (GRAM) the triangle of their dot products
+  // candidates' key rows or (Gram) the triangle of their dot products
   extern __shared__ __align__(16) unsigned char dyn[];
   const int g = blockIdx.x % h_kv, p = blockIdx.x / h_kv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -399,7 +289,6 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
   float* cst = reinterpret_cast<float*>(dyn + (size_t)max_cand * 8);
   unsigned char* region = dyn + (((size_t)max_cand * 12 + 15) & ~(size_t)15);
   uint32_t* skeys = reinterpret_cast<uint32_t*>(region);
-  T* ckeys = reinterpret_cast<T*>(region);
   const bool take_all = (C >= n_cand);
   float den = 0.f;
   if (cand_in) {
@@ -658,22 +547,18 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
   // C <= 2 NT steps (2 NT = 128 NW words each)
   uint32_t* trace_slot = &sh.hist[0][0];
   uint32_t* trace_key = &sh.hist[0][0] + kWaves * 128;
+  // s~ of candidate c: its base score, pooled as in phase 0, over the normaliser
+  auto stilde = [&](int c) -> float {
+    if (cand_in) return cst[c] / den;  // the entry's score (no pooling with candidate lists)
+    const int pos = cpos[c];
+    float sv = base_score(pos);
+    for (int j = max(0, pos - pool_h); j <= min(n_cand - 1, pos + pool_h); ++j) sv = fmaxf(sv, base_score(j));
+    return sv / den;
+  };
   int last = -1;
-  if constexpr (GRAM) {
+  if constexpr (MODE == kGram) {
     static_assert(DT == kDtBf16, "the Gram greedy takes bf16 keys");
-    // s~ of every candidate (its base score, pooled as in phase 0, over the normaliser)
-    for (int c = tid; c < C; c += kThreads) {
-      const int pos = cpos[c];
-      float sv;
-      if (cand_in) {
-        sv = cst[c];  // the entry's score (no pooling with candidate lists)
-      } else {
-        sv = base_score(pos);
-        for (int j = max(0, pos - pool_h); j <= min(n_cand - 1, pos + pool_h); ++j)
-          sv = fmaxf(sv, base_score(j));
-      }
-      cst[c] = sv / den;
-    }
+    for (int c = tid; c < C; c += kThreads) cst[c] = stilde(c);
     gram::cosines<D, kWaves>(kg, cpos, C, cinv, region, tid);
     const float* tri = reinterpret_cast<const float*>(region) + 1;
     if (wave == 0) {
@@ -723,127 +608,31 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
     }
     __syncthreads();
   } else {
-    KeyRow<DT, D> key[CPT];
-    float st[CPT], corr[CPT], inv[CPT];
-    bool admitted[CPT];
-#pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-      const int c = tid + q * kThreads;
-      admitted[q] = c >= C;  // slots beyond C never compete
-      corr[q] = 0.f;
-      st[q] = 0.f;
-      inv[q] = 0.f;
-      if (c < C) {
-        const int pos = cpos[c];
-        key[q].load(kg + (size_t)pos * D);
-        key[q].store(ckeys + (size_t)c * D);
-        const float n2 = key[q].sq_norm();
-        inv[q] = n2 > 0.f ? 1.f / sqrtf(n2) : 0.f;  // a zero key has cosine 0 to everything
-        cinv[c] = inv[q];
-        float sv;
-        if (cand_in) {
-          sv = cst[c];  // the entry's score (no pooling with candidate lists)
-        } else {
-          sv = base_score(pos);
-          for (int j = max(0, pos - pool_h); j <= min(n_cand - 1, pos + pool_h); ++j)
-            sv = fmaxf(sv, base_score(j));
-        }
-        st[q] = sv / den;
-      }
-    }
+    constexpr int QT = quad_threads(DT);
+    static_assert(QT <= NT, "the greedy's threads are the workgroup's first");
+    for (int c = tid; c < C; c += kThreads) cst[c] = stilde(c);
     __syncthreads();
-
-    float last_inv = 0.f;
-    // only the waves that own candidate slots take part; the others just keep step with the
-    // barrier (sleeping there instead of taking issue slots from the live waves)
-    const int live_waves = min(kWaves, (C + 63) / 64);
-    const bool live = wave < live_waves;
-    for (int t = 0; t < bp; ++t) {
-      if (live) {
-        float my_score = -INFINITY;  // admitted slots rank below every live score
-        int my_slot = 0x7FFFFFFF;
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-          if (!admitted[q]) {
-            if (last >= 0) {
-              const float cs = key[q].dot_lds(ckeys + (size_t)last * D) * inv[q] * last_inv;
-              corr[q] = fmaxf(corr[q], cs);
-            }
-            float sc = fmaf(lam2, corr[q], st[q]);
-            if (!(sc > -INFINITY)) sc = -FLT_MAX;  // NaN or -inf still ranks above admitted slots
-            if (sc > my_score) {  // q ascending: ties keep the lower slot
-              my_score = sc;
-              my_slot = tid + q * kThreads;
-            }
-          }
-        }
-        const uint64_t wbest = wave_best<CPT == 1>(my_score, my_slot);
-        // the wave's best slot is owned by one of its lanes (slot = tid + q NT): its 1 / |k| rides
-        // along, so that no lookup follows the barrier
-        const int bslot = unpack_slot(wbest);
-        float binv = 0.f;
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-          const uint32_t v = __builtin_amdgcn_readlane(__float_as_uint(inv[q]), bslot & 63);
-          if ((bslot - q * kThreads) >> 6 == wave) binv = __uint_as_float(v);
-        }
-        if (lane == 0)
-          sh.best[t & 1][wave] = make_uint4((uint32_t)wbest, (uint32_t)(wbest >> 32), __float_as_uint(binv), 0u);
-      }
-      __syncthreads();
-      if (live) {
-        // the live waves' records (score key, slot, 1 / |k|), four reads in flight at a time
-        uint64_t b = 0;
-        float bi = 0.f;
-        for (int v0 = 0; v0 < live_waves; v0 += 4) {
-          // records past the live waves are read (v0 + 3 < NW) but never win
-          uint4 r[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) r[u] = sh.best[t & 1][v0 + u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const uint64_t o = v0 + u < live_waves ? ((uint64_t)r[u].y << 32) | r[u].x : 0ull;
-            if (o > b) {
-              b = o;
-              bi = __uint_as_float(r[u].z);
-            }
-          }
-        }
-        last = min(max(unpack_slot(b), 0), C - 1);  // always a live slot: bp <= C
-#pragma unroll
-        for (int q = 0; q < CPT; ++q)
-          if (tid + q * kThreads == last) admitted[q] = true;
-        last_inv = bi;
-        if (tid == 0) {  // the step's record; written out after the last step
-          trace_slot[t] = (uint32_t)last;
-          trace_key[t] = (uint32_t)(b >> 32);
-        }
-      }
-    }
+    constexpr bool kRows = MODE == kQuadRows;
+    quad::Greedy<DT, D, QT, J, kRows> gr;
+    gr.run(kg, cpos, cst, cinv, C, bp, lam2, *reinterpret_cast<quad::Shared<DT, D, QT, kRows>*>(region),
+           trace_slot, trace_key, tid, kThreads, cand_idx || cand_corr);
     if (cand_idx || cand_corr) {
-      // corr after the last step includes the last admitted key
-#pragma unroll
-      for (int q = 0; q < CPT; ++q) {
-        if (!admitted[q]) {
-          const float cs = key[q].dot_lds(ckeys + (size_t)last * D) * inv[q] * last_inv;
-          corr[q] = fmaxf(corr[q], cs);
-        }
-      }
       const size_t o = ((size_t)p * h_kv + g) * cand_stride;
+      if (tid < QT) {
 #pragma unroll
-      for (int q = 0; q < CPT; ++q) {
-        const int c = tid + q * kThreads;
-        if (c < cand_stride) {
-          if (cand_idx) cand_idx[o + c] = c < C ? cpos[c] : -1;
-          if (cand_corr) cand_corr[o + c] = c < C ? corr[q] : 0.f;
+        for (int j = 0; j < J; ++j) {
+          const int c = tid + j * QT;
+          if (c < cand_stride) {
+            if (cand_idx) cand_idx[o + c] = c < C ? cpos[c] : -1;
+            if (cand_corr) cand_corr[o + c] = c < C ? gr.corr[j] : 0.f;
+          }
         }
       }
-      for (int c = tid + CPT * kThreads; c < cand_stride; c += kThreads) {
+      for (int c = tid + J * QT; c < cand_stride; c += kThreads) {
         if (cand_idx) cand_idx[o + c] = -1;
         if (cand_corr) cand_corr[o + c] = 0.f;
       }
     }
-
   }
   __syncthreads();
   for (int t = tid; t < bp; t += kThreads) {
@@ -904,7 +693,7 @@ __global__ __launch_bounds__(NT) void mmr_select_kernel(
 // ------------------------------------------------------------------------------------------------
 int select_max_candidates(int d, int elem_bytes) {
   const int by_lds = kMaxCandBytes / (d * elem_bytes);
-  const int by_regs = elem_bytes == 2 ? 1024 : 4 * 256;  // candidate slots of the workgroup
+  const int by_regs = 1024;
   return by_lds < by_regs ? by_lds : by_regs;
 }
 
@@ -912,7 +701,7 @@ namespace {
 // Bytes of dynamic LDS before the region: positions, 1 / |k| and s~ of max_cand candidates.
 size_t lds_head(int max_cand) { return ((size_t)max_cand * 12 + 15) & ~(size_t)15; }
 
-template <int DT, int D, int NT, int CPT, bool STAGED, bool GRAM>
+template <int DT, int D, int NT, int J, bool STAGED, int MODE>
 hipError_t select_launch(const Shape& s, const SelectArgs& a, size_t body, hipStream_t st) {
   using T = typename Elem<DT>::T;
   // the region also holds the compaction's slot bitmap, its word prefixes and the positions
@@ -920,7 +709,7 @@ hipError_t select_launch(const Shape& s, const SelectArgs& a, size_t body, hipSt
       std::max(std::max(body, STAGED ? (size_t)a.max_cand_all * 4 : (size_t)0),
                (size_t)(2 * kMaxSlotWords + a.max_cand) * 4);
   const size_t dyn = lds_head(a.max_cand) + region;
-  auto kern = mmr_select_kernel<DT, D, NT, CPT, STAGED, GRAM>;
+  auto kern = mmr_select_kernel<DT, D, NT, J, STAGED, MODE>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
   if (e != hipSuccess) return e;
@@ -936,38 +725,52 @@ hipError_t select_launch(const Shape& s, const SelectArgs& a, size_t body, hipSt
   return hipGetLastError();
 }
 
+// Bytes of LDS of the greedy besides the candidates' positions and scores.
+template <int DT, int D, int MODE> size_t greedy_bytes(int max_cand) {
+  if constexpr (MODE == kGram) return gram::region_bytes<D>(max_cand);
+  else return quad::Shared<DT, D, quad_threads(DT), MODE == kQuadRows>::bytes(max_cand);
+}
+
 // Score keys are staged in LDS when every problem's candidates fit next to the key rows or the
 // Gram triangle (and the whole workgroup's LDS stays within the 160 KiB of a CU).
-template <int DT, int D, int NT, int CPT, bool GRAM>
+template <int DT, int D, int NT, int J, int MODE>
 hipError_t select_dispatch(const Shape& s, const SelectArgs& a, hipStream_t st) {
-  using T = typename Elem<DT>::T;
-  const size_t body = GRAM ? gram::region_bytes<D>(a.max_cand) : (size_t)a.max_cand * D * sizeof(T);
+  const size_t body = greedy_bytes<DT, D, MODE>(a.max_cand);
   const size_t staged = lds_head(a.max_cand) + std::max(body, (size_t)a.max_cand_all * 4) +
                         sizeof(SelectShared<NT / 64>);
   if ((size_t)a.max_cand_all * 4 <= (size_t)kMaxStagedKeyBytes && staged <= kLdsBytes)
-    return select_launch<DT, D, NT, CPT, true, GRAM>(s, a, body, st);
-  return select_launch<DT, D, NT, CPT, false, GRAM>(s, a, body, st);
+    return select_launch<DT, D, NT, J, true, MODE>(s, a, body, st);
+  return select_launch<DT, D, NT, J, false, MODE>(s, a, body, st);
+}
+
+// The quad greedy, J candidates per thread.  From candidate lists the scoring's other threads would
+// only wait, and without the staged scores two workgroups fit a CU unless the rows take its LDS: so
+// the rows stay out where there are more units than CUs (a step takes 0.95 us instead of 0.73, but two
+// units' steps overlap).
+template <int DT, int D, int J>
+hipError_t select_quad(const Shape& s, const SelectArgs& a, hipStream_t st) {
+  constexpr int kQT = quad_threads(DT), kNT = DT == kDtBf16 ? 1024 : 256;
+  if (a.cand_in) {
+    constexpr int kCUs = 256;
+    if ((int64_t)s.n_prob * s.h_kv > kCUs)
+      return select_launch<DT, D, kQT, J, false, kQuadBest>(s, a, greedy_bytes<DT, D, kQuadBest>(a.max_cand), st);
+    return select_launch<DT, D, kQT, J, false, kQuadRows>(s, a, greedy_bytes<DT, D, kQuadRows>(a.max_cand), st);
+  }
+  return select_dispatch<DT, D, kNT, J, kQuadRows>(s, a, st);
 }
 
 template <int DT, int D>
 hipError_t select_cpt(const Shape& s, const SelectArgs& a, hipStream_t st) {
   constexpr int kMaxCand = kMaxCandBytes / (D * (int)sizeof(typename Elem<DT>::T));
+  constexpr int kQT = quad_threads(DT);
+  static_assert(kMaxCand <= 2 * kQT, "at most two candidates per thread of the greedy");
   if constexpr (DT == kDtBf16) {
-    // bf16 key rows fit the registers of 16 waves: one candidate per thread of 1024
-    static_assert(kMaxCand <= 1024, "one candidate per thread");
-    if (a.max_cand <= gram::kMaxCand) return select_dispatch<DT, D, 1024, 1, true>(s, a, st);
-    return select_dispatch<DT, D, 1024, 1, false>(s, a, st);
-  } else {
-    // only the candidates-per-thread counts that the LDS key copy allows are instantiated
-    constexpr int kNT = 256;
-    const int cpt = (a.max_cand + kNT - 1) / kNT;
-    if (cpt <= 1) return select_dispatch<DT, D, kNT, 1, false>(s, a, st);
-    if constexpr (kMaxCand > kNT) {
-      if (cpt <= 2) return select_dispatch<DT, D, kNT, 2, false>(s, a, st);
-    }
-    if constexpr (kMaxCand > 2 * kNT) return select_dispatch<DT, D, kNT, 4, false>(s, a, st);
-    return hipErrorInvalidValue;
+    if (a.max_cand <= gram::kMaxCand) return select_dispatch<DT, D, 1024, 1, kGram>(s, a, st);
   }
+  if constexpr (kMaxCand > kQT) {
+    if (a.max_cand > kQT) return select_quad<DT, D, 2>(s, a, st);
+  }
+  return select_quad<DT, D, 1>(s, a, st);
 }
 }  // namespace
 

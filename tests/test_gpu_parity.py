@@ -533,3 +533,18 @@ def test_candidates_cut_in_the_window_kernel(h_q, h_kv, d, lens, budget, cand_mu
     run = gpu_cases.run_gpu(wl, cand_mult=cand_mult, timed=True)
     assert "cands_sel_idx" in run.host
     _all(run)
+
+
+@pytest.mark.parametrize("n_layers", [1, 132])
+@pytest.mark.parametrize("dtype,d,lens,budget", [
+    ("bf16", 128, [1100, 640], 65), ("bf16", 128, [700], 128), ("bf16", 64, [1300, 900], 100),
+    ("bf16", 64, [1300, 1100], 200), ("f32", 64, [300, 200], 16), ("f32", 64, [700, 500], 100),
+    ("f32", 128, [300], 60)])
+def test_greedy_against_the_last_admitted_row(dtype, d, lens, budget, n_layers):
+    """The greedy that forms cosines in every step (bf16 above 256 candidates, fp32): one and two
+    candidates per thread, counts that leave quads and waves partly empty (C = 64 .. 800), from the
+    scores and from candidate lists, the rows in LDS (few units) and only the waves' best ones (264
+    units and more): every route the same bits, and the oracle's."""
+    wl = _shape_workload(4, 2, d, len(lens), n_layers, lens, budget=budget)
+    wl.dtype = workloads.BF16 if dtype == "bf16" else workloads.F32
+    _all_of(gpu_cases.run_gpu(wl, timed=True), [0, wl.n_prob - 1])
