@@ -458,10 +458,8 @@ int kv_window_mu_sigma_ex(const kv_problem* pr, const void* q_win, const void* k
                                                     nullptr, row_max, row_sum, mu, sigma, all, hs));
   }
   // other shapes: chunked row statistics, then a second pass over K
-  st = launch_status(kv::launch_window_stats(s, q_win, k, scale, ws, row_max, row_sum, hs));
-  if (st != KV_OK) return st;
-  return launch_status(kv::launch_mu_sigma(s, q_win, k, scale, row_max, row_sum, mu, sigma,
-                                           nullptr, all, hs));
+  return launch_status(kv::launch_window_passes(s, q_win, k, scale, ws, row_max, row_sum, mu, sigma,
+                                                all, nullptr, hs));
 }
 
 int kv_window_mu_sigma_noalloc(const kv_problem* pr, const void* q_win, const void* k, float scale,
@@ -506,9 +504,12 @@ int kv_window_base_scores(const kv_problem* pr, const void* q_win, const void* k
                                                          lambda1, w_mu, row_max, row_sum, score,
                                                          all, hs));
   const size_t win = window_ws_bytes(pr, s);
-  if (kv::stream_shape_ok(s, scale)) {
-    // several segments per unit: the one-launch path in base-score mode when the grid fits
-    const kv::ScoreMode sm{score, lambda1, w_mu};
+  const kv::ScoreMode sm{score, lambda1, w_mu};
+  if (!kv::stream_shape_ok(s, scale))  // the chunked kernels form them in their second pass
+    return launch_status(kv::launch_window_passes(s, q_win, k, scale, ws, row_max, row_sum, nullptr,
+                                                  nullptr, all, &sm, hs));
+  {
+    // several workgroups per unit: the one-launch path in base-score mode when the grid fits
     bool launched = false;
     st = launch_status(kv::launch_stream_window_coop(s, stream_plan_of(pr, s), q_win, k, scale, ws,
                                                      row_max, row_sum, nullptr, nullptr, all,

@@ -26,6 +26,14 @@ struct Shape {
   int max_chunks() const { return (max_len + kWindowChunk - 1) / kWindowChunk; }
 };
 
+// Base-score mode of a second pass: s = fma(lambda1[p], sigma, w_mu mu) per key into score instead of
+// mu / sigma (score == nullptr: off).
+struct ScoreMode {
+  float* score = nullptr;
+  const float* lambda1 = nullptr;
+  float w_mu = 1.f;
+};
+
 // Workspace bytes of the split-L row statistics.
 size_t window_stats_ws_bytes(const Shape& s);
 
@@ -37,6 +45,12 @@ hipError_t launch_mu_sigma(const Shape& s, const void* q_win, const void* k, flo
                            float* attn, bool sigma_all, hipStream_t stream);
 
 constexpr int kStreamMaxPerWg = 3;  // segments whose statistics a one-workgroup unit can hold
+
+// Both passes of the chunked kernels: launch_window_stats, then launch_mu_sigma or (sm) the base
+// scores; units of few chunks merge their row statistics in the second pass.
+hipError_t launch_window_passes(const Shape& s, const void* q_win, const void* k, float scale,
+                                void* ws, float* row_max, float* row_sum, float* mu, float* sigma,
+                                bool sigma_all, const ScoreMode* sm, hipStream_t stream);
 
 // Streaming two-pass row statistics + mu/sigma (bf16, scale > 0, w = 32 with G in {1, 2, 4} or w in
 // {8, 16} with G w <= 64): every unit is cut into segments of seg_keys keys (a multiple of 256), one
@@ -122,11 +136,6 @@ hipError_t launch_base_scores(const Shape& s, const float* mu, const float* sigm
 // it computes their partials itself.  Sets *launched = false (and launches nothing) if the grid
 // does not fit the chip at once; the caller then takes the two-launch path.
 // With sm (base-score mode) the second pass stores scores instead of mu / sigma.
-struct ScoreMode {
-  float* score;
-  const float* lambda1;
-  float w_mu;
-};
 hipError_t launch_stream_window_coop(const Shape& s, const StreamPlan& plan, const void* q_win,
                                      const void* k, float scale, void* ws, float* row_max,
                                      float* row_sum, float* mu, float* sigma, bool sigma_all,

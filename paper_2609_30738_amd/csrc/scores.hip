@@ -1,6 +1,5 @@
 // Base scores from mu / sigma rows (section 3.2, Eq. (5)), for batches whose window statistics
-// come from the chunked window path or the two-launch streaming path (the other paths form them
-// inside their second pass).
+// come from the two-launch streaming path (the other paths form them inside their second pass).
 #include <algorithm>
 
 #include "common.h"

@@ -28,7 +28,8 @@ template <typename T, int D> struct Lds {
   static constexpr int PITCH = D + 16 / (int)sizeof(T);  // padded row (elements): no bank conflicts
 };
 
-// Stage the R = G*w window rows of kv group g (contiguous in q_win) into LDS, zero-padding to NB*32.
+// Stage NB*32 of the R = G*w window rows of kv group g (contiguous in q_win; qg: the first of them,
+// R: how many follow) into LDS, zero-padded.
 template <typename T, int D, int NB>
 __device__ __forceinline__ void stage_queries(const T* __restrict__ qg, int R, T* q_lds) {
   constexpr int VEC = 16 / (int)sizeof(T);
@@ -52,22 +53,23 @@ template <int DT, int D, int NB>
 __global__ __launch_bounds__(kThreads) void window_stats_kernel(
     const typename Elem<DT>::T* __restrict__ q_win, const typename Elem<DT>::T* __restrict__ k,
     const int32_t* __restrict__ lens, const int64_t* __restrict__ tok_off, int h_q, int h_kv, int w,
-    float c, int chunk_keys, int max_chunks, float2* __restrict__ partial) {
+    float c, int chunk_keys, int max_chunks, int splits, float2* __restrict__ partial) {
   using T = typename Elem<DT>::T;
-  constexpr int ROWS = NB * 32;
+  constexpr int ROWS = NB * 32;  // the workgroup's rows, of splits * ROWS padded rows of the unit
   constexpr int PITCH = Lds<T, D>::PITCH;
   __shared__ __align__(16) T q_lds[ROWS * PITCH];
   __shared__ float2 wave_part[kWaves][ROWS];
 
-  const int chunk = blockIdx.x, g = blockIdx.y, p = blockIdx.z;
+  const int chunk = blockIdx.x / splits, row0 = (blockIdx.x % splits) * ROWS;
+  const int g = blockIdx.y, p = blockIdx.z;
   const int L = lens[p];
   const int k0 = chunk * chunk_keys;
   if (k0 >= L) return;
   const int k1 = min(k0 + chunk_keys, L);
-  const int G = h_q / h_kv, R = G * w;
+  const int G = h_q / h_kv, R = G * w - row0;  // rows from row0 on
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
 
-  stage_queries<T, D, NB>(q_win + ((size_t)p * h_q + (size_t)g * G) * w * D, R, q_lds);
+  stage_queries<T, D, NB>(q_win + (((size_t)p * h_q + (size_t)g * G) * w + row0) * D, R, q_lds);
   const T* kg = k + ((size_t)tok_off[p] * h_kv + (size_t)g * L) * D;
 
   // This lane's window row in every N block and the last key that row may see (causal mask).
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(kThreads) void window_stats_kernel(
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int m = b * 32 + l32;
-    lim[b] = (m < R) ? (L - w + (m % w)) : -1;
+    lim[b] = (m < R) ? (L - w + ((row0 + m) % w)) : -1;
   }
   float m_run[NB], z_run[NB];
 #pragma unroll
@@ -141,8 +143,22 @@ __global__ __launch_bounds__(kThreads) void window_stats_kernel(
       const float2 o = wave_part[v][threadIdx.x];
       merge_mz(acc.x, acc.y, o.x, o.y);
     }
-    partial[(((size_t)p * h_kv + g) * max_chunks + chunk) * ROWS + threadIdx.x] = acc;
+    partial[(((size_t)p * h_kv + g) * max_chunks + chunk) * (splits * ROWS) + row0 + threadIdx.x] = acc;
   }
+}
+
+// The (m, z) of a row over its chunks' partials, `stride` entries apart, merged in order.
+__device__ __forceinline__ float2 merge_chunks(const float2* src, int n_chunks, int stride) {
+  float M = -INFINITY, Z = 0.f;
+  for (int ch0 = 0; ch0 < n_chunks; ch0 += 4) {  // four loads in flight
+    float2 o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      o[u] = ch0 + u < n_chunks ? src[(size_t)(ch0 + u) * stride] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) merge_mz(M, Z, o[u].x, o[u].y);
+  }
+  return make_float2(M, Z);
 }
 
 // One thread per (problem, q head, window row): merge the chunk partials.
@@ -157,29 +173,30 @@ __global__ __launch_bounds__(kThreads) void combine_stats_kernel(
   const int h = rem / w, r = rem % w;
   const int G = h_q / h_kv, g = h / G, m = (h % G) * w + r;
   const int n_chunks = (lens[p] + chunk_keys - 1) / chunk_keys;
-  float M = -INFINITY, Z = 0.f;
-  const float2* src = partial + ((size_t)p * h_kv + g) * max_chunks * rows_pad + m;
-  for (int ch0 = 0; ch0 < n_chunks; ch0 += 4) {  // four loads in flight
-    float2 o[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      o[u] = ch0 + u < n_chunks ? src[(size_t)(ch0 + u) * rows_pad] : make_float2(-INFINITY, 0.f);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) merge_mz(M, Z, o[u].x, o[u].y);
-  }
-  row_max[idx] = M * kLn2;
-  row_sum[idx] = Z;
+  const float2 v = merge_chunks(partial + ((size_t)p * h_kv + g) * max_chunks * rows_pad + m, n_chunks, rows_pad);
+  row_max[idx] = v.x * kLn2;
+  row_sum[idx] = v.y;
 }
 
 // ------------------------------------------------------------------------------------------------
 // Pass 2: attention, group mean, mean and sample dispersion over the window
 // ------------------------------------------------------------------------------------------------
+// Row statistics to merge from pass 1's partials (partial == nullptr: given as row_max / row_sum),
+// and where chunk 0 writes them.
+struct MergeIn {
+  const float2* partial = nullptr;
+  int chunk_keys = 0, max_chunks = 0;
+  float* row_max = nullptr;
+  float* row_sum = nullptr;
+};
+
 template <int DT, int D, int NB, bool W32, bool ALL>
 __global__ __launch_bounds__(kThreads) void mu_sigma_kernel(
     const typename Elem<DT>::T* __restrict__ q_win, const typename Elem<DT>::T* __restrict__ k,
     const int32_t* __restrict__ lens, const int64_t* __restrict__ tok_off, int h_q, int h_kv, int w,
     float c, int chunk_keys, const float* __restrict__ row_max, const float* __restrict__ row_sum,
-    float* __restrict__ mu, float* __restrict__ sigma, float* __restrict__ attn) {
+    MergeIn mi, float* __restrict__ mu, float* __restrict__ sigma, ScoreMode sm,
+    float* __restrict__ attn) {
   using T = typename Elem<DT>::T;
   constexpr int ROWS = NB * 32;
   constexpr int PITCH = Lds<T, D>::PITCH;
@@ -201,10 +218,35 @@ __global__ __launch_bounds__(kThreads) void mu_sigma_kernel(
     float b = INFINITY;  // padded rows contribute 2^(-inf) = 0
     if (m < R) {
       const size_t ri = ((size_t)p * h_q + (size_t)g * G + m / w) * w + (m % w);
-      b = row_max[ri] * kLog2e + log2f(row_sum[ri]);
+      float rm, rs;
+      if (mi.partial) {
+        // the chunk partials of the row, merged as combine_stats_kernel merges them
+        const float2 v = merge_chunks(mi.partial + ((size_t)p * h_kv + g) * mi.max_chunks * ROWS + m,
+                                      (L + mi.chunk_keys - 1) / mi.chunk_keys, ROWS);
+        rm = v.x * kLn2;
+        rs = v.y;
+        if (chunk == 0) {
+          mi.row_max[ri] = rm;
+          mi.row_sum[ri] = rs;
+        }
+      } else {
+        rm = row_max[ri];
+        rs = row_sum[ri];
+      }
+      b = rm * kLog2e + log2f(rs);
     }
     bsh[m] = b;
   }
+  const float lam1 = sm.score ? sm.lambda1[p] : 0.f;
+  // mu and sigma of a key, or its base score (the rounding of base_score_kernel)
+  auto put = [&](size_t at, float mean, float sd) __attribute__((always_inline)) {
+    if (sm.score) {
+      sm.score[at] = fmaf(lam1, sd, sm.w_mu * mean);
+    } else {
+      mu[at] = mean;
+      sigma[at] = sd;
+    }
+  };
   const T* kg = k + ((size_t)tok_off[p] * h_kv + (size_t)g * L) * D;
   const size_t stat_base = (size_t)tok_off[p] * h_kv + (size_t)g * L;
   float* attn_g = attn ? attn + (size_t)tok_off[p] * h_q * w + (size_t)g * G * w * L : nullptr;
@@ -287,8 +329,7 @@ __global__ __launch_bounds__(kThreads) void mu_sigma_kernel(
       v = (v + swap_halves(v)) * inv_w1;
       if constexpr (ALL) v = h_m2 / (float)(R - 1);
       if (half == 0 && key_ok) {
-        mu[stat_base + key] = mean;
-        sigma[stat_base + key] = sqrtf(v);
+        put(stat_base + key, mean, sqrtf(v));
       }
     } else {
       // the tile's values were written by other lanes of this wave
@@ -304,8 +345,7 @@ __global__ __launch_bounds__(kThreads) void mu_sigma_kernel(
           const float dlt = red[wave][m][l32] - mean;
           v += dlt * dlt;
         }
-        mu[stat_base + key] = mean;
-        sigma[stat_base + key] = sqrtf(v / (float)(R - 1));
+        put(stat_base + key, mean, sqrtf(v / (float)(R - 1)));
       } else if (half == 0 && key_ok) {
         float s = 0.f;
         for (int r = 0; r < w; ++r) {
@@ -321,8 +361,7 @@ __global__ __launch_bounds__(kThreads) void mu_sigma_kernel(
           const float dlt = ab * inv_g - mean;
           v += dlt * dlt;
         }
-        mu[stat_base + key] = mean;
-        sigma[stat_base + key] = sqrtf(v * inv_w1);
+        put(stat_base + key, mean, sqrtf(v * inv_w1));
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -341,61 +380,90 @@ size_t window_stats_ws_bytes(const Shape& s) {
 
 namespace {
 
+// Workgroups below which a launch is cut finer: one to a CU.  Finer cuts than that stage the queries
+// more often than they overlap: 256 chunks of 1024 fp32 keys (G = 4, d = 128) take 94 us in pass 1
+// and 125 in pass 2, cut into 1024 workgroups 103 and 159; one chunk of 512 keys 18.7 us in pass 2,
+// as four workgroups 7.6.
+constexpr int64_t kFillWgs = 256;
+
 template <int DT, int D, int NB>
-hipError_t stats_dispatch(const Shape& s, const void* q, const void* k, float scale, void* ws,
-                          float* row_max, float* row_sum, hipStream_t st) {
+void stats_launch(const Shape& s, const void* q, const void* k, float scale, int splits, void* ws,
+                  hipStream_t st) {
   using T = typename Elem<DT>::T;
-  const dim3 grid(s.max_chunks(), s.h_kv, s.n_prob);
+  const dim3 grid(s.max_chunks() * splits, s.h_kv, s.n_prob);
   window_stats_kernel<DT, D, NB><<<grid, kThreads, 0, st>>>(
       static_cast<const T*>(q), static_cast<const T*>(k), s.lens, s.tok_off, s.h_q, s.h_kv, s.w,
-      scale * kLog2e, kWindowChunk, s.max_chunks(), static_cast<float2*>(ws));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t rows = (int64_t)s.n_prob * s.h_q * s.w;
-  combine_stats_kernel<<<(unsigned)((rows + kThreads - 1) / kThreads), kThreads, 0, st>>>(
-      static_cast<const float2*>(ws), s.lens, s.n_prob, s.h_q, s.h_kv, s.w, NB * 32,
-      kWindowChunk, s.max_chunks(), row_max, row_sum);
+      scale * kLog2e, kWindowChunk, s.max_chunks(), splits, static_cast<float2*>(ws));
+}
+
+// Pass 1: the chunk partials.  The chunk stays the unit of the statistics; where the chunks leave CUs
+// idle, every block of 32 rows gets a workgroup of its own (each streams the keys again, from the
+// caches).
+template <int DT, int D>
+hipError_t stats_nb(const Shape& s, const void* q, const void* k, float scale, void* ws, hipStream_t st) {
+  const int nb = s.row_blocks();
+  const bool split = (int64_t)s.n_prob * s.h_kv * s.max_chunks() < kFillWgs;
+  if (nb == 1 || split) stats_launch<DT, D, 1>(s, q, k, scale, nb, ws, st);
+  else if (nb == 2) stats_launch<DT, D, 2>(s, q, k, scale, 1, ws, st);
+  else stats_launch<DT, D, 4>(s, q, k, scale, 1, ws, st);
   return hipGetLastError();
 }
+
+struct MuSigmaIn {
+  const float* row_max;
+  const float* row_sum;
+  MergeIn mi;
+  float* mu;
+  float* sigma;
+  ScoreMode sm;
+  float* attn;
+  bool all;
+};
 
 template <int DT, int D, int NB, bool W32>
 hipError_t mu_sigma_dispatch(const Shape& s, const void* q, const void* k, float scale,
-                             const float* row_max, const float* row_sum, float* mu,
-                             float* sigma, float* attn, bool all, hipStream_t st) {
+                             const MuSigmaIn& a, hipStream_t st) {
   using T = typename Elem<DT>::T;
-  const dim3 grid(s.max_chunks(), s.h_kv, s.n_prob);
-  auto kern = all ? mu_sigma_kernel<DT, D, NB, W32, true> : mu_sigma_kernel<DT, D, NB, W32, false>;
+  // keys per workgroup: kWindowChunk, or down to one tile per wave while that fills the chip (the
+  // keys are independent of each other)
+  int keys = kWindowChunk;
+  while (keys > kWaves * 32 &&
+         (int64_t)s.n_prob * s.h_kv * ((s.max_len + keys - 1) / keys) < kFillWgs)
+    keys /= 2;
+  const dim3 grid((s.max_len + keys - 1) / keys, s.h_kv, s.n_prob);
+  auto kern = a.all ? mu_sigma_kernel<DT, D, NB, W32, true> : mu_sigma_kernel<DT, D, NB, W32, false>;
   kern<<<grid, kThreads, 0, st>>>(
       static_cast<const T*>(q), static_cast<const T*>(k), s.lens, s.tok_off, s.h_q, s.h_kv, s.w,
-      scale * kLog2e, kWindowChunk, row_max, row_sum, mu, sigma, attn);
+      scale * kLog2e, keys, a.row_max, a.row_sum, a.mi, a.mu, a.sigma, a.sm, a.attn);
   return hipGetLastError();
 }
 
 template <int DT, int D>
-hipError_t stats_nb(const Shape& s, const void* q, const void* k, float scale, void* ws,
-                    float* rm, float* rs, hipStream_t st) {
-  switch (s.row_blocks()) {
-    case 1: return stats_dispatch<DT, D, 1>(s, q, k, scale, ws, rm, rs, st);
-    case 2: return stats_dispatch<DT, D, 2>(s, q, k, scale, ws, rm, rs, st);
-    default: return stats_dispatch<DT, D, 4>(s, q, k, scale, ws, rm, rs, st);
-  }
-}
-
-template <int DT, int D>
-hipError_t mu_sigma_nb(const Shape& s, const void* q, const void* k, float scale,
-                       const float* rm, const float* rs, float* mu, float* sg, float* attn,
-                       bool all, hipStream_t st) {
+hipError_t mu_sigma_nb(const Shape& s, const void* q, const void* k, float scale, const MuSigmaIn& a,
+                       hipStream_t st) {
   const int nb = s.row_blocks();
   if (s.w == 32) {
     switch (nb) {
-      case 1: return mu_sigma_dispatch<DT, D, 1, true>(s, q, k, scale, rm, rs, mu, sg, attn, all, st);
-      case 2: return mu_sigma_dispatch<DT, D, 2, true>(s, q, k, scale, rm, rs, mu, sg, attn, all, st);
-      default: return mu_sigma_dispatch<DT, D, 4, true>(s, q, k, scale, rm, rs, mu, sg, attn, all, st);
+      case 1: return mu_sigma_dispatch<DT, D, 1, true>(s, q, k, scale, a, st);
+      case 2: return mu_sigma_dispatch<DT, D, 2, true>(s, q, k, scale, a, st);
+      default: return mu_sigma_dispatch<DT, D, 4, true>(s, q, k, scale, a, st);
     }
   }
-  if (nb == 1)
-    return mu_sigma_dispatch<DT, D, 1, false>(s, q, k, scale, rm, rs, mu, sg, attn, all, st);
-  return mu_sigma_dispatch<DT, D, 2, false>(s, q, k, scale, rm, rs, mu, sg, attn, all, st);
+  if (nb == 1) return mu_sigma_dispatch<DT, D, 1, false>(s, q, k, scale, a, st);
+  return mu_sigma_dispatch<DT, D, 2, false>(s, q, k, scale, a, st);
+}
+
+hipError_t stats_for(const Shape& s, const void* q, const void* k, float scale, void* ws, hipStream_t st) {
+  if (s.dtype == kDtBf16)
+    return s.d == 64 ? stats_nb<kDtBf16, 64>(s, q, k, scale, ws, st) : stats_nb<kDtBf16, 128>(s, q, k, scale, ws, st);
+  return s.d == 64 ? stats_nb<kDtF32, 64>(s, q, k, scale, ws, st) : stats_nb<kDtF32, 128>(s, q, k, scale, ws, st);
+}
+
+hipError_t mu_sigma_for(const Shape& s, const void* q, const void* k, float scale, const MuSigmaIn& a,
+                        hipStream_t st) {
+  if (s.dtype == kDtBf16)
+    return s.d == 64 ? mu_sigma_nb<kDtBf16, 64>(s, q, k, scale, a, st) : mu_sigma_nb<kDtBf16, 128>(s, q, k, scale, a, st);
+  return s.d == 64 ? mu_sigma_nb<kDtF32, 64>(s, q, k, scale, a, st) : mu_sigma_nb<kDtF32, 128>(s, q, k, scale, a, st);
 }
 
 }  // namespace
@@ -412,24 +480,34 @@ hipError_t launch_combine_partials(const Shape& s, const void* part, int chunk_k
 
 hipError_t launch_window_stats(const Shape& s, const void* q_win, const void* k, float scale,
                                void* ws, float* row_max, float* row_sum, hipStream_t stream) {
-  if (s.dtype == kDtBf16)
-    return s.d == 64 ? stats_nb<kDtBf16, 64>(s, q_win, k, scale, ws, row_max, row_sum, stream)
-                     : stats_nb<kDtBf16, 128>(s, q_win, k, scale, ws, row_max, row_sum, stream);
-  return s.d == 64 ? stats_nb<kDtF32, 64>(s, q_win, k, scale, ws, row_max, row_sum, stream)
-                   : stats_nb<kDtF32, 128>(s, q_win, k, scale, ws, row_max, row_sum, stream);
+  hipError_t e = stats_for(s, q_win, k, scale, ws, stream);
+  if (e != hipSuccess) return e;
+  return launch_combine_partials(s, ws, kWindowChunk, s.max_chunks(), s.row_blocks() * 32, row_max,
+                                 row_sum, stream);
 }
 
 hipError_t launch_mu_sigma(const Shape& s, const void* q_win, const void* k, float scale,
                            const float* row_max, const float* row_sum, float* mu, float* sigma,
                            float* attn, bool sigma_all, hipStream_t stream) {
-  const bool all = sigma_all;
-  if (s.dtype == kDtBf16)
-    return s.d == 64
-               ? mu_sigma_nb<kDtBf16, 64>(s, q_win, k, scale, row_max, row_sum, mu, sigma, attn, all, stream)
-               : mu_sigma_nb<kDtBf16, 128>(s, q_win, k, scale, row_max, row_sum, mu, sigma, attn, all, stream);
-  return s.d == 64
-             ? mu_sigma_nb<kDtF32, 64>(s, q_win, k, scale, row_max, row_sum, mu, sigma, attn, all, stream)
-             : mu_sigma_nb<kDtF32, 128>(s, q_win, k, scale, row_max, row_sum, mu, sigma, attn, all, stream);
+  return mu_sigma_for(s, q_win, k, scale,
+                      MuSigmaIn{row_max, row_sum, MergeIn{}, mu, sigma, ScoreMode{}, attn, sigma_all}, stream);
+}
+
+hipError_t launch_window_passes(const Shape& s, const void* q_win, const void* k, float scale,
+                                void* ws, float* row_max, float* row_sum, float* mu, float* sigma,
+                                bool sigma_all, const ScoreMode* sm, hipStream_t stream) {
+  // every workgroup of pass 2 merges its unit's rows itself while their chunks are few
+  constexpr int kMergeChunks = 16;
+  MuSigmaIn a{row_max, row_sum, MergeIn{}, mu, sigma, sm ? *sm : ScoreMode{}, nullptr, sigma_all};
+  hipError_t e;
+  if (s.max_chunks() <= kMergeChunks) {
+    e = stats_for(s, q_win, k, scale, ws, stream);
+    a.mi = MergeIn{static_cast<const float2*>(ws), kWindowChunk, s.max_chunks(), row_max, row_sum};
+  } else {
+    e = launch_window_stats(s, q_win, k, scale, ws, row_max, row_sum, stream);
+  }
+  if (e != hipSuccess) return e;
+  return mu_sigma_for(s, q_win, k, scale, a, stream);
 }
 
 }  // namespace kv

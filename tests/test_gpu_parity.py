@@ -548,3 +548,18 @@ def test_greedy_against_the_last_admitted_row(dtype, d, lens, budget, n_layers):
     wl = _shape_workload(4, 2, d, len(lens), n_layers, lens, budget=budget)
     wl.dtype = workloads.BF16 if dtype == "bf16" else workloads.F32
     _all_of(gpu_cases.run_gpu(wl, timed=True), [0, wl.n_prob - 1])
+
+
+@pytest.mark.parametrize("dtype,h_q,w", [("f32", 6, 20), ("bf16", 6, 20), ("f32", 2, 64), ("bf16", 4, 5),
+                                         ("f32", 8, 32)])
+@pytest.mark.parametrize("lens", [[2100, 333], [20000]])
+def test_chunked_windows(dtype, h_q, w, lens):
+    """Shapes of the chunked kernels (windows that are no power of two, fp32, one to four 32-row
+    blocks): row blocks in workgroups of their own, second-pass workgroups of few keys, the row
+    statistics merged in the second pass (up to 16 chunks) or by the combine kernel (20 chunks)."""
+    import dataclasses
+    wl = dataclasses.replace(_shape_workload(h_q, 2, 64, len(lens), 1, lens), w=w)
+    wl.dtype = workloads.BF16 if dtype == "bf16" else workloads.F32
+    for sigma_rows in ("group_mean", "all_rows"):
+        _all_of(gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows), None)
+    _all_of(gpu_cases.run_gpu(wl, fused=False), None)
