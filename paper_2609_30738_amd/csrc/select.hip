@@ -115,6 +115,39 @@ constexpr int kFastBins = 2048;  // 11-bit digit
 constexpr int kFastShift = 21;
 constexpr int kListCap = 1024;   // members of the cut's bin ranked exactly
 
+// The bin of the C-th largest key counted in h[kFastBins] into sh.sel_threshold, how many of its
+// members the C take into sh.sel_need and their number into sh.wave_cnt[1][0].  Starts and ends
+// synchronised.
+template <int NW>
+__device__ __forceinline__ void cut_bin(SelectShared<NW>& sh, const uint32_t* h, int C, int tid, int lane,
+                                        int wave) {
+  // suffix sums over the bins (larger bins = larger keys): thread t owns bins 2t, 2t + 1
+  const uint32_t c0 = h[2 * tid], c1 = h[2 * tid + 1];
+  uint32_t suf = c0 + c1;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_down(suf, off, 64);
+    if (lane + off < 64) suf += o;
+  }
+  if (lane == 0) sh.scan[wave] = suf;
+  __syncthreads();
+  uint32_t above = 0;
+  for (int v = wave + 1; v < NW; ++v) above += sh.scan[v];
+  const uint32_t gt_hi = suf - (c0 + c1) + above;  // keys in bins above 2t + 1
+  const uint32_t gt_lo = gt_hi + c1;               // keys in bins above 2t
+  if (gt_hi < (uint32_t)C && gt_hi + c1 >= (uint32_t)C) {
+    sh.sel_threshold = 2 * tid + 1;
+    sh.sel_need = C - (int)gt_hi;
+    sh.wave_cnt[1][0] = c1;
+  }
+  if (gt_lo < (uint32_t)C && gt_lo + c0 >= (uint32_t)C) {
+    sh.sel_threshold = 2 * tid;
+    sh.sel_need = C - (int)gt_lo;
+    sh.wave_cnt[1][0] = c0;
+  }
+  __syncthreads();
+}
+
 // The candidate positions (C of the n_cand staged keys, the largest keys, ties to the lower
 // position) in ascending order into cpos, when the bin of the C-th largest key under an 11-bit
 // digit holds at most kListCap keys; returns false (having written nothing the general path
@@ -143,31 +176,7 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
       wave_hist_add_hot(h, kk[q] >> kFastShift, i0 + q * NT + tid < n_cand, hot, lane);
   }
   __syncthreads();
-  // suffix sums over the bins (larger bins = larger keys): thread t owns bins 2t, 2t + 1
-  const uint32_t c0 = h[2 * tid], c1 = h[2 * tid + 1];
-  uint32_t suf = c0 + c1;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = __shfl_down(suf, off, 64);
-    if (lane + off < 64) suf += o;
-  }
-  if (lane == 0) sh.scan[wave] = suf;
-  __syncthreads();
-  uint32_t above = 0;
-  for (int v = wave + 1; v < NW; ++v) above += sh.scan[v];
-  const uint32_t gt_hi = suf - (c0 + c1) + above;  // keys in bins above 2t + 1
-  const uint32_t gt_lo = gt_hi + c1;               // keys in bins above 2t
-  if (gt_hi < (uint32_t)C && gt_hi + c1 >= (uint32_t)C) {
-    sh.sel_threshold = 2 * tid + 1;
-    sh.sel_need = C - (int)gt_hi;
-    sh.wave_cnt[1][0] = c1;
-  }
-  if (gt_lo < (uint32_t)C && gt_lo + c0 >= (uint32_t)C) {
-    sh.sel_threshold = 2 * tid;
-    sh.sel_need = C - (int)gt_lo;
-    sh.wave_cnt[1][0] = c0;
-  }
-  __syncthreads();
+  cut_bin(sh, h, C, tid, lane, wave);
   const uint32_t bin = sh.sel_threshold;
   const int need = sh.sel_need;
   const int members = (int)sh.wave_cnt[1][0];
@@ -232,6 +241,110 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
       m &= m - 1;
     }
   }
+  __syncthreads();
+  return true;
+}
+
+// The same from scores in memory, for units whose keys do not fit in LDS (no pooling): one pass counts
+// the keys and takes the maximum score (local_max, per thread), a second collects the candidates.
+// load4(v, sc) gives the scores of positions 4 v + e - off (e = 0 .. 3; off: how far the row starts
+// past a 16-byte boundary); positions outside [0, n_cand) are ignored.  Eight units of 100001 keys
+// spent 140 us here re-reading them element by element for four radix digits and two collecting
+// passes, now about 60.
+// (n_cand > 16384 >= C.)
+template <int NW, class Load4>
+__device__ bool memory_candidates(SelectShared<NW>& sh, Load4&& load4, int off, int32_t* cpos, int n_cand,
+                                  int C, float& local_max, int tid, int lane, int wave) {
+  constexpr int NT = NW * 64, U = 4;  // 16-byte loads of a thread in flight
+  uint32_t* h = &sh.hist[0][0];
+  uint64_t* list = reinterpret_cast<uint64_t*>(h + kFastBins);
+  for (int i = tid; i < kFastBins; i += NT) h[i] = 0u;
+  if (tid < 2) sh.wave_cnt[0][tid] = 0u;  // append counters: candidates above the bin, list
+  __syncthreads();
+  const int nv = (n_cand + off + 3) / 4;
+  // fn(score, position, valid) over all positions, whole waves; then(v0) after every U NT loads
+  auto pass = [&](auto&& fn, auto&& then) __attribute__((always_inline)) {
+    for (int v0 = 0; v0 < nv; v0 += U * NT) {
+      float sc[U][4];
+#pragma unroll
+      for (int q = 0; q < U; ++q) load4(v0 + q * NT + tid, sc[q]);
+#pragma unroll
+      for (int q = 0; q < U; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * (v0 + q * NT + tid) + e - off;
+          fn(sc[q][e], i, i >= 0 && i < n_cand);
+        }
+      then(v0);
+    }
+  };
+  // the first 16 k keys are all counted; the bin of their C-th largest bounds the cut from below, so
+  // of the others only the keys from it on count (whole waves mostly have none)
+  uint32_t hot = ~0u;  // no digit yet
+  float lmax = -INFINITY;
+  uint32_t least = 0;
+  pass(
+      [&](float sv, int, bool in) __attribute__((always_inline)) {
+        if (in) lmax = fmaxf(lmax, sv);
+        const uint32_t b = order_key(sv) >> kFastShift;
+        in = in && b >= least;
+        if (__ballot(in)) wave_hist_add_hot(h, b, in, hot, lane);
+      },
+      [&](int v0) __attribute__((always_inline)) {
+        if (v0 == 0) {
+          __syncthreads();
+          cut_bin(sh, h, C, tid, lane, wave);
+          least = sh.sel_threshold;
+        }
+      });
+  local_max = lmax;
+  __syncthreads();
+  cut_bin(sh, h, C, tid, lane, wave);
+  const uint32_t bin = sh.sel_threshold;
+  const int need = sh.sel_need;
+  const int members = (int)sh.wave_cnt[1][0];
+  if (members > kListCap) return false;
+  pass(
+      [&](float sv, int i, bool in) __attribute__((always_inline)) {
+        const uint32_t key = order_key(sv), b = key >> kFastShift;
+        if (__ballot(in && b >= bin) == 0) return;  // most waves hold none
+        wave_append(in && b > bin, &sh.wave_cnt[0][0], lane, [&](uint32_t slot) { cpos[slot] = i; });
+        wave_append(in && b == bin, &sh.wave_cnt[0][1], lane,
+                    [&](uint32_t slot) { list[slot] = ((uint64_t)(~key) << 32) | (uint32_t)i; });
+      },
+      [](int) {});
+  __syncthreads();
+  // the `need` smallest of the list (key descending, then position), then all C positions ascending:
+  // each entry's rank is the number of entries before it, counted by NT threads in shares
+  auto share = [&](int n, auto&& fn) __attribute__((always_inline)) {  // fn(entry, first, last) of a share
+    const int parts = max(1, NT / max(1, n));
+    for (int x = tid; x < parts * n; x += NT) fn(x % n, (x / n) * n / parts, (x / n + 1) * n / parts);
+  };
+  uint32_t* rank = h;          // the histogram is dead
+  uint32_t* pos = h + kListCap;
+  for (int i = tid; i < kListCap; i += NT) rank[i] = 0u;
+  __syncthreads();
+  share(members, [&](int i, int j0, int j1) __attribute__((always_inline)) {
+    const uint64_t own = list[i];
+    uint32_t n = 0;
+    for (int j = j0; j < j1; ++j) n += list[j] < own ? 1u : 0u;
+    if (n) atomicAdd(&rank[i], n);
+  });
+  __syncthreads();
+  for (int i = tid; i < members; i += NT)
+    if (rank[i] < (uint32_t)need) cpos[C - need + (int)rank[i]] = (int32_t)(uint32_t)list[i];
+  __syncthreads();
+  for (int i = tid; i < kListCap; i += NT) rank[i] = 0u;
+  for (int i = tid; i < C; i += NT) pos[i] = (uint32_t)cpos[i];
+  __syncthreads();
+  share(C, [&](int i, int j0, int j1) __attribute__((always_inline)) {
+    const uint32_t own = pos[i];
+    uint32_t n = 0;
+    for (int j = j0; j < j1; ++j) n += pos[j] < own ? 1u : 0u;
+    if (n) atomicAdd(&rank[i], n);
+  });
+  __syncthreads();
+  for (int i = tid; i < C; i += NT) cpos[rank[i]] = (int32_t)pos[i];
   __syncthreads();
   return true;
 }
@@ -347,8 +460,40 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 2) void mmr_select_kernel(
       skeys[i] = order_key(sv);
     }
     __syncthreads();
-  } else {
-    for (int i = tid; i < n_cand; i += kThreads) local_max = fmaxf(local_max, base_score(i));
+  }
+  // scores that stay in memory: cut by two wide passes over them (1024 threads, no pooling)
+  bool fast_done = false;
+  if constexpr (!STAGED) {
+    if (NT == 1024 && !take_all && pool_h == 0 && n_cand > 16384) {
+      const int off = (int)(base & 3);
+      const float* row = (sc_g ? sc_g : mu_g) - off;
+      const float* row2 = sc_g ? nullptr : sg_g - off;
+      auto load4 = [&](int v, float (&o)[4]) __attribute__((always_inline)) {
+        const int i = 4 * v - off;
+        if (i >= 0 && i + 3 < n_cand) {
+          const float4 x = *reinterpret_cast<const float4*>(row + 4 * (size_t)v);
+          if (row2) {
+            const float4 y = *reinterpret_cast<const float4*>(row2 + 4 * (size_t)v);
+            o[0] = fmaf(lam1, y.x, w_mu * x.x);
+            o[1] = fmaf(lam1, y.y, w_mu * x.y);
+            o[2] = fmaf(lam1, y.z, w_mu * x.z);
+            o[3] = fmaf(lam1, y.w, w_mu * x.w);
+          } else {
+            o[0] = x.x;
+            o[1] = x.y;
+            o[2] = x.z;
+            o[3] = x.w;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = i + e >= 0 && i + e < n_cand ? base_score(i + e) : 0.f;
+        }
+      };
+      if constexpr (NT == 1024)
+        fast_done = memory_candidates<kWaves>(sh, load4, off, cpos, n_cand, C, local_max, tid, lane, wave);
+    } else {
+      for (int i = tid; i < n_cand; i += kThreads) local_max = fmaxf(local_max, base_score(i));
+    }
   }
   // Max-pooling keeps the largest score of the window, whose key is also the largest key.
   if constexpr (STAGED) {
@@ -406,7 +551,6 @@ __global__ __launch_bounds__(NT, NT >= 512 ? 4 : 2) void mmr_select_kernel(
   //      members (a few hundred where salient tokens set the cut) are sorted exactly, by key and then
   //      position, in LDS.  The candidates are then sorted by position.  A bin too full for the
   //      list (a cut through the flat bulk of the scores) takes the general path below.
-  bool fast_done = false;
   if constexpr (STAGED && NT == 1024) {
     if (!take_all) fast_done = fast_candidates<kWaves>(sh, skeys, cpos, n_cand, C, tid, lane, wave);
   }

@@ -566,3 +566,16 @@ def test_chunked_windows(dtype, h_q, w, lens):
     for sigma_rows in ("group_mean", "all_rows"):
         _all_of(gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows), None)
     _all_of(gpu_cases.run_gpu(wl, fused=False), None)
+
+
+@pytest.mark.parametrize("d,lens,budget,density", [(64, [36001, 35003], 16, 0.02), (64, [40003], 200, 0.02),
+                                                   (128, [36003], 37, 0.02), (64, [36001], 64, 0.0)])
+def test_cut_of_long_units_from_memory(d, lens, budget, density):
+    """Units whose score keys do not fit in LDS: the cut reads the scores twice (rows that start off
+    a 16-byte boundary, odd lengths), from scores and from mu / sigma, with a few members in the
+    cut's bin and (no planted keys: every score in one bin) too many, where the general digit passes
+    take over."""
+    import dataclasses
+    wl = _shape_workload(4, 2, d, len(lens), 1, lens, budget=budget)
+    wl = dataclasses.replace(wl, layout=workloads.Layout(cluster_density=density) if density else workloads.Layout())
+    _all_of(gpu_cases.run_gpu(wl, timed=True), None)
