@@ -293,7 +293,9 @@ int kv_mmr_select_scored(const kv_problem* pr, const float* score, const void* k
  * For bf16 batches of w = 32 that kv_window_base_scores scores inside the window kernel's second
  * pass, with cand_mult > 0 and L_p <= 32768, the keys are read once in full, the candidates
  * are cut inside that launch (a second pass revisits only the 32-key tiles whose score bound
- * reaches the cut) and no score is stored; otherwise the scores go through the workspace and the
+ * reaches the cut) and no score is stored; batches of w = 32 whose units span several
+ * workgroups of many more tiles than candidates read the keys once in full as well (two launches,
+ * then the cut); otherwise the scores go through the workspace and the
  * selection kernel's first phases cut the candidates from them.  Calls that overlap on one
  * workspace race. */
 int kv_window_candidates(const kv_problem* pr, const void* q_win, const void* k, float scale,

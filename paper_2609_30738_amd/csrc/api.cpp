@@ -306,9 +306,18 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   // need not come back from memory)
   float* score = reinterpret_cast<float*>(base + head);
   const size_t score_bytes = align_up((size_t)token_extent(pr) * pr->h_kv * sizeof(float));
-  st = kv_window_base_scores(pr, q_win, k, scale, lambda1, w_mu, sigma_rows, row_max, row_sum,
-                             score, base + head + score_bytes, ws_bytes - head - score_bytes,
-                             stream);
+  char* rest = base + head + score_bytes;  // kv_window_base_scores' workspace: window part, mu, sigma
+  const kv::StreamPlan plan = kv::stream_shape_ok(s, scale) ? stream_plan_of(pr, s) : kv::StreamPlan{};
+  const size_t win = window_ws_bytes(pr, s);
+  if (kv::stream_shape_ok(s, scale) && s.w == 32 && cand_mult > 0 && kv::prune_segs_ok(plan, stride) &&
+      kv::prune_segs_bytes(s) <= base_scores_ws_bytes(pr, s, false) - win) {
+    // only the scores that can reach the cut (the codes take the place of mu and sigma)
+    st = launch_status(kv::launch_prune_segs(s, plan, q_win, k, scale, lambda1, w_mu, budget, b_dev, cand_mult,
+                                             keep_tail, rest, rest + win, row_max, row_sum, score, all, hs));
+  } else {
+    st = kv_window_base_scores(pr, q_win, k, scale, lambda1, w_mu, sigma_rows, row_max, row_sum, score, rest,
+                               ws_bytes - head - score_bytes, stream);
+  }
   if (st != KV_OK) return st;
   ScoreSource src;
   src.score = score;

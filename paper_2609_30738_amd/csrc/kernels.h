@@ -127,6 +127,17 @@ hipError_t launch_stream_window_cands(const Shape& s, const StreamPlan& plan, co
                                       uint64_t* cand_out, float* cand_max, int cand_stride,
                                       uint32_t* codes, bool sigma_all, const CandSelect* sel,
                                       hipStream_t stream);
+// Row statistics and the base scores of every key that can be among a unit's C_p best, -inf for the
+// others, for units of several workgroups (plan.max_wgs > 1, w = 32), in two launches that read the
+// keys once in full.  part_ws: the segment partials (stream_ws_bytes); codes_ws: prune_segs_bytes of
+// scratch (16-byte aligned).  prune_segs_ok: whether the plan suits it (max_cand: the largest C_p).
+bool prune_segs_ok(const StreamPlan& plan, int max_cand);
+size_t prune_segs_bytes(const Shape& s);
+hipError_t launch_prune_segs(const Shape& s, const StreamPlan& plan, const void* q_win, const void* k,
+                             float scale, const float* lambda1, float w_mu, int budget,
+                             const int32_t* budgets, int cand_mult, int keep_tail, void* part_ws,
+                             void* codes_ws, float* row_max, float* row_sum, float* score,
+                             bool sigma_all, hipStream_t stream);
 // Base scores s = fma(lambda1[p], sigma, w_mu mu) of every key from mu / sigma rows (for batches
 // that take the other window paths).
 hipError_t launch_base_scores(const Shape& s, const float* mu, const float* sigma,

@@ -20,126 +20,11 @@
 // On the 32-layer Mistral-shaped pass at L = 32768 (C = 256) the bounds leave about one tile in
 // twenty to pass 2.
 #include "select_gram.h"
-#include "stream_passes.h"
+#include "stream_bounds.h"
 
 namespace kv {
 namespace stream {
 namespace {
-
-constexpr int kPruneMaxTiles = kCandMaxLen / kTileKeys;
-// Order of the tiles for pass 2: bin 0 holds the tiles with a masked key (bound +inf), bin k >= 1
-// the tiles whose bound lies within ((k - 1) / 16, k / 16] octaves below the largest finite bound
-// (the last bin: everything further below).
-constexpr int kOrderBins = 1024;
-constexpr float kBinsPerOctave = 16.f;
-// Bounds are widened by kBoundSlack for the rounding of both passes (logits formed in another
-// MFMA operand order, approximate exp2 / log2) and kept above kBoundFloor.
-constexpr float kBoundSlack = 1.00390625f;  // 1 + 2^-8
-constexpr float kBoundFloor = 0x1p-100f;
-constexpr float kCodeStep = 0.125f;          // code units: 1/8 of a factor of two
-
-// Pass-1 hook of candidate mode: per tile, the largest t = logit * c of every (head, window row) as
-// the number of 1/8-steps it lies below the tile's largest t (rounded down, one less where the
-// exact number is an odd integer; at most 255), one byte per head of the row's word in the unit's
-// code rows, and the tile's largest t into ref[tile] (LDS); a tile with a masked key gets
-// ref = +inf and a tile with a NaN logit ref = NaN (both always revisited).  The row maxima of two
-// heads are merged across the wave's halves in one exchange, leaving head k in lanes 0-31 and head
-// k + NB / 2 in lanes 32-63, so each lane stores the bytes of its row's word that belong to its
-// heads (one store per tile).
-template <int NBH> struct TileCodes {
-  static constexpr int kStores = 1;
-  static_assert(NBH == 1 || NBH == 2 || NBH == 4, "one, two or four query heads per key head");
-  uint32_t* codes;  // tile i at codes + 32 i: word r = window row r, byte b < NB = head b
-  float* ref;       // [n_tiles] LDS
-  float c;          // softmax scale * log2(e)
-  int l32, lane;
-
-  template <int NB>
-  __device__ __forceinline__ void interior(int tile, const float (&tmax)[NB]) const {
-    static_assert(NB == NBH, "head count");
-    constexpr int NP = NB == 4 ? 2 : 1;  // heads per lane after the exchange
-    float tm[NP];  // row maxima of t over the tile's 32 keys
-    if constexpr (NB == 1) {
-      tm[0] = max_halves(tmax[0]) * c;
-    } else {
-#pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax[k]),
-                                                        __float_as_uint(tmax[k + NB / 2]), false, false);
-        tm[k] = __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1])) * c;
-      }
-    }
-    const float m = NP == 2 ? __builtin_elementwise_maximum(tm[0], tm[NP - 1]) : tm[0];
-    float r = wave_max_uniform(m);  // the tile's largest t
-    if (__ballot(m != m)) r = __builtin_nanf("");
-    // code: the steps (r - t) * 8 less half a step, rounded to nearest (even) and saturated to
-    // [0, 255] by v_cvt_pk_u8_f32: never above the exact number of steps (NaN gives 0)
-    uint32_t w = 0u;
-#pragma unroll
-    for (int k = 0; k < NP; ++k)
-      w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(r - tm[k], 1.f / kCodeStep, -0.5f), (uint32_t)k, w);
-    char* dst = reinterpret_cast<char*>(codes + 32 * tile + l32);
-    if constexpr (NB == 4) store_u16(dst + 2 * (lane >> 5), w);
-    else if constexpr (NB == 2) store_u8(dst + (lane >> 5), w);
-    else store_u8(dst, w);
-    if (lane == 0) ref[tile] = r;
-  }
-  __device__ __forceinline__ void guarded(int tile) const {
-    store_word(codes + 32 * tile + l32, 0xFFFFFFFFu);
-    if (lane == 0) ref[tile] = INFINITY;
-  }
-  __device__ __forceinline__ static void store_word(uint32_t* dst, uint32_t v) {
-    asm volatile("global_store_dword %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
-  }
-  __device__ __forceinline__ static void store_u16(char* dst, uint32_t v) {
-    asm volatile("global_store_short %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
-  }
-  __device__ __forceinline__ static void store_u8(char* dst, uint32_t v) {
-    asm volatile("global_store_byte %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
-  }
-};
-
-// Upper bound of the base score s = w_mu mu + lambda1 sigma (section 3.2, Eq. (5)) of every key of
-// a tile from its codes (row r of head h: t <= ref - code / 8) and the final row normalisers b:
-// a[h][r] = 2^(t - b[h][r]) <= a'[h][r], hence mu <= (1 / 32) sum_r abar'[r] (abar': mean over the
-// G heads) and, since a variance is at most the mean square, sigma <= sqrt(sum_r abar'[r]^2 / 31)
-// (sum_{h,r} a'^2 / (32 G - 1) for the dispersion over all rows).  The positive parts of w_mu and
-// lambda1 enter.
-template <int NB, bool ALL>
-__device__ __forceinline__ float tile_bound(const uint32_t* codes_t, float ref, const float* bsh,
-                                            float wmu_p, float lam1_p, float inv_g) {
-  const uint4* src = reinterpret_cast<const uint4*>(codes_t);
-  float p1 = 0.f, p2 = 0.f;
-#pragma unroll 2
-  for (int v = 0; v < 8; ++v) {
-    const uint4 w4 = src[v];
-    const uint32_t ws[4] = {w4.x, w4.y, w4.z, w4.w};
-    float arow[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const float4 bv = *reinterpret_cast<const float4*>(bsh + b * 32 + 4 * v);
-      const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float code = (float)((ws[e] >> (8 * b)) & 0xFFu);
-        const float a = __builtin_amdgcn_exp2f(fmaf(code, -kCodeStep, ref) - bb[e]);
-        arow[e] += a;
-        if constexpr (ALL) p2 = fmaf(a, a, p2);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      p1 += arow[e];
-      if constexpr (!ALL) {
-        const float ab = arow[e] * inv_g;
-        p2 = fmaf(ab, ab, p2);
-      }
-    }
-  }
-  constexpr float inv_n1 = ALL ? 1.f / (float)(NB * 32 - 1) : 1.f / 31.f;
-  const float mu_b = p1 * inv_g * (1.f / 32.f);
-  return fmaf(fmaf(lam1_p, __builtin_sqrtf(p2 * inv_n1), wmu_p * mu_b), kBoundSlack, kBoundFloor);
-}
 
 // Bitmap words over the candidate positions of a unit (one bit per position).
 constexpr int kBitmapWords = kCandMaxLen / 32;
@@ -177,8 +62,6 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   using Gm = SGeo<D, NB>;
   constexpr int R = Gm::R, NS = Gm::NS, NT = NW * 64;
   constexpr int kRedWords = NW * R * 2;
-  constexpr int kTilesPerThread = kPruneMaxTiles / NT;
-  static_assert(kPruneMaxTiles % NT == 0, "whole tiles per thread");
   static_assert(NT % kTileKeys == 0, "whole tiles per visit");
   static_assert(kTileKeys == 32, "a half-wave visits the keys of one tile");
   static_assert(2 * kOrderBins >= kBitmapWords + 2 * kRankDirect,
@@ -262,82 +145,9 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   int n_ord;   // tiles in the order of pass 2
   float smax;  // the lane's largest evaluated score
   if constexpr (PRUNE) {
-  // ---- bounds of the thread's tiles tid + u NT (-inf: no candidate key, never revisited)
-  uint32_t* cnt = bins;                  // [kOrderBins] tiles per bin
-  uint32_t* off = bins + kOrderBins;     // [kOrderBins] first position of each bin, then a cursor
-  for (int i = tid; i < kOrderBins; i += NT) cnt[i] = 0u;
-  const float wmu_p = fmaxf(a.w_mu, 0.f), lam1_p = fmaxf(lam1, 0.f);
-  float bnd[kTilesPerThread];
-  float lmax = 0.f;  // largest finite bound (bounds are positive)
-#pragma unroll
-  for (int u = 0; u < kTilesPerThread; ++u) {
-    const int i = tid + u * NT;
-    bnd[u] = -INFINITY;
-    if (i < n_tiles && i * kTileKeys < n_cand) {
-      const float r = ub[i];
-      float bd = INFINITY;
-      if (r < INFINITY) bd = tile_bound<NB, ALL>(codes_u + 32 * i, r, bsh, wmu_p, lam1_p, inv_g);
-      if (!(bd == bd)) bd = INFINITY;  // NaN inputs: revisit
-      bnd[u] = bd;
-      if (bd < INFINITY) lmax = fmaxf(lmax, bd);
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) lmax = fmaxf(lmax, __shfl_xor(lmax, o, 64));
-  if (lane == 0) atomicMax(&bmax_bits, __float_as_uint(lmax));  // positive floats order as integers
-  __syncthreads();
-  const float bmax = __uint_as_float(bmax_bits);
-  const float lg_max = __builtin_amdgcn_logf(bmax);  // log2; only used when a finite bound exists
-  int bin[kTilesPerThread];
-#pragma unroll
-  for (int u = 0; u < kTilesPerThread; ++u) {
-    bin[u] = -1;
-    if (bnd[u] == INFINITY) {
-      bin[u] = 0;
-    } else if (bnd[u] > 0.f) {
-      // bins counted down from the largest bound, rounded towards the larger bound (the bin's
-      // upper edge stays above every bound in it despite the rounding of log2)
-      const float x = (lg_max - __builtin_amdgcn_logf(bnd[u])) * kBinsPerOctave - (1.f / 64.f);
-      bin[u] = 1 + (int)fminf(fmaxf(x, 0.f), (float)(kOrderBins - 2));
-    }
-    if (bin[u] >= 0) atomicAdd(&cnt[bin[u]], 1u);
-  }
-  __syncthreads();
-  if (wave == 0) {
-    // exclusive scan of the counts: lane l holds bins 16 l .. 16 l + 15
-    constexpr int PB = kOrderBins / 64;
-    uint32_t v[PB];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < PB; ++k) {
-      v[k] = cnt[lane * PB + k];
-      s += v[k];
-    }
-    uint32_t incl = s;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = (uint32_t)__shfl_up((int)incl, o, 64);
-      if (lane >= o) incl += t;
-    }
-    uint32_t run = incl - s;
-#pragma unroll
-    for (int k = 0; k < PB; ++k) {
-      off[lane * PB + k] = run;
-      run += v[k];
-    }
-    if (lane == 63) n_eval = incl;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kTilesPerThread; ++u) {
-    if (bin[u] >= 0) {
-      const uint32_t pos = atomicAdd(&off[bin[u]], 1u);
-      order[pos] = (uint16_t)(tid + u * NT);
-      ub[pos] = bin[u] == 0 ? INFINITY
-                            : bmax * __builtin_amdgcn_exp2f(-(float)(bin[u] - 1) * (1.f / kBinsPerOctave));
-    }
-  }
-  __syncthreads();  // the order is complete; the ring is free
+  // ---- bounds of the tiles and their order
+  const float bmax = order_tiles<NB, ALL, NT>(codes_u, n_tiles, 0, n_cand, bsh, a.w_mu, lam1, inv_g, ub,
+                                              order, bins, &bmax_bits, &n_eval, tid);  // the ring is free
 
   // ---- pass 2: exact scores of the wanted tiles, stored over their codes
   n_ord = (int)n_eval;

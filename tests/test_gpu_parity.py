@@ -579,3 +579,17 @@ def test_cut_of_long_units_from_memory(d, lens, budget, density):
     wl = _shape_workload(4, 2, d, len(lens), 1, lens, budget=budget)
     wl = dataclasses.replace(wl, layout=workloads.Layout(cluster_density=density) if density else workloads.Layout())
     _all_of(gpu_cases.run_gpu(wl, timed=True), None)
+
+
+@pytest.mark.parametrize("sigma_rows", ["group_mean", "all_rows"])
+@pytest.mark.parametrize("h_q,h_kv,d,n_layers,lens,budget,cand_mult", [
+    (32, 8, 128, 8, [40001], 16, 4), (8, 8, 64, 10, [30001], 8, 3), (16, 8, 64, 8, [36005], 30, 3)])
+def test_units_of_several_workgroups_revisit_few_tiles(h_q, h_kv, d, n_layers, lens, budget, cand_mult,
+                                                       sigma_rows):
+    """64 and 80 units of four segments each (one or two to a workgroup): the first launch codes the
+    tiles, the second revisits those that can hold a candidate; the selection equals that from all
+    scores (kv_mmr_select_scored, kv_mmr_select_ex) bit for bit, and the oracle's, also where the
+    cut falls in the flat scores of a workgroup's own keys."""
+    wl = _shape_workload(h_q, h_kv, d, len(lens), n_layers, lens, budget=budget)
+    assert lens[0] * 64 // 256 // 32 >= 3 * cand_mult * budget  # tiles of a workgroup against C
+    _all_of(gpu_cases.run_gpu(wl, timed=True, cand_mult=cand_mult, sigma_rows=sigma_rows), [0, wl.n_prob - 1])
