@@ -115,6 +115,28 @@ constexpr int kFastBins = 2048;  // 11-bit digit
 constexpr int kFastShift = 21;
 constexpr int kListCap = 1024;   // members of the cut's bin ranked exactly
 
+// Entries up to which counting the smaller ones beats a bitonic sort (n * n / NT reads of a thread
+// against log2 n (log2 n + 1) / 2 barriers): at n = 384 144 reads, which issue back to back, against
+// the 45 barriers of a sort of 512.
+constexpr int kRankMax = 384;
+
+// rank[i] = how many of v[0, n) are smaller than v[i] (all different), n <= kRankMax, counted by the
+// NT threads in shares.  rank: n words of LDS; starts after v is visible, ends synchronised.
+template <int NT, typename V>
+__device__ __forceinline__ void rank_entries(const V* v, int n, uint32_t* rank, int tid) {
+  for (int i = tid; i < n; i += NT) rank[i] = 0u;
+  __syncthreads();
+  const int parts = max(1, NT / max(1, n));
+  for (int x = tid; x < parts * n; x += NT) {
+    const int i = x % n, part = x / n, j1 = (part + 1) * n / parts;
+    const V own = v[i];
+    uint32_t smaller = 0;
+    for (int j = part * n / parts; j < j1; ++j) smaller += v[j] < own ? 1u : 0u;
+    if (smaller) atomicAdd(&rank[i], smaller);
+  }
+  __syncthreads();
+}
+
 // The bin of the C-th largest key counted in h[kFastBins] into sh.sel_threshold, how many of its
 // members the C take into sh.sel_need and their number into sh.wave_cnt[1][0].  Starts and ends
 // synchronised.
@@ -163,7 +185,11 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
   for (int i = tid; i < kFastBins; i += NT) h[i] = 0u;
   if (tid < 2) sh.wave_cnt[0][tid] = 0u;  // append counters: candidates above the bin, list
   __syncthreads();
+  // the first 4096 keys are all counted; the bin of their C-th largest bounds the cut from below, so of
+  // the others only the keys from it on count (whole waves mostly have none).  With the short lists
+  // ranked: one layer of 32768 keys (B = 64) 94.9 -> 89.5 us, 32 layers of 8192 255 -> 238 us.
   uint32_t hot = ~0u;  // no digit yet
+  uint32_t least = 0;
   for (int i0 = 0; i0 < n_cand; i0 += 4 * NT) {
     uint32_t kk[4];
 #pragma unroll
@@ -172,8 +198,15 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
       kk[q] = i < n_cand ? skeys[i] : 0u;
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      wave_hist_add_hot(h, kk[q] >> kFastShift, i0 + q * NT + tid < n_cand, hot, lane);
+    for (int q = 0; q < 4; ++q) {
+      const bool in = i0 + q * NT + tid < n_cand && (kk[q] >> kFastShift) >= least;
+      if (__ballot(in)) wave_hist_add_hot(h, kk[q] >> kFastShift, in, hot, lane);
+    }
+    if (i0 == 0 && n_cand > 8 * NT) {
+      __syncthreads();
+      cut_bin(sh, h, C, tid, lane, wave);
+      least = sh.sel_threshold;
+    }
   }
   __syncthreads();
   cut_bin(sh, h, C, tid, lane, wave);
@@ -194,17 +227,14 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
     for (int q = 0; q < 4; ++q) {
       const int i = i0 + q * NT + tid;
       const bool in = i < n_cand;
+      if (__ballot(in && (kk[q] >> kFastShift) >= bin) == 0) continue;  // most waves hold none
       wave_append(in && (kk[q] >> kFastShift) > bin, &sh.wave_cnt[0][0], lane,
                   [&](uint32_t slot) { cpos[slot] = i; });
       wave_append(in && (kk[q] >> kFastShift) == bin, &sh.wave_cnt[0][1], lane,
                   [&](uint32_t slot) { list[slot] = ((uint64_t)(~kk[q]) << 32) | (uint32_t)i; });
     }
   }
-  int n2 = 1;
-  while (n2 < members) n2 <<= 1;
-  for (int i = members + tid; i < n2; i += NT) list[i] = ~0ull;
   __syncthreads();
-  bitonic_sort(list, n2, tid, NT);
   // the candidates in ascending position order: a bitmap over the positions (the histogram's
   // space, free again: n_cand <= kMaxStagedKeyBytes / 4 positions), then each thread writes the
   // set positions of its words at its offset
@@ -213,11 +243,23 @@ __device__ bool fast_candidates(SelectShared<NW>& sh, const uint32_t* skeys, int
   static_assert(kWords * 4 <= kFastBins * 4, "bitmap space");
   const int words = (n_cand + 31) / 32;
   for (int w = tid; w < words; w += NT) bits[w] = 0u;
-  __syncthreads();
-  for (int t = tid; t < C; t += NT) {
-    const int pos = t < C - need ? cpos[t] : (int32_t)(uint32_t)list[t - (C - need)];
-    atomicOr(&bits[pos >> 5], 1u << (pos & 31));
+  auto mark = [&](int pos) __attribute__((always_inline)) { atomicOr(&bits[pos >> 5], 1u << (pos & 31)); };
+  // the `need` smallest entries of the list
+  if (members <= kRankMax) {
+    static_assert(kWords + kRankMax <= kFastBins, "the ranks fit after the bitmap");
+    uint32_t* rank = h + kWords;
+    rank_entries<NT>(list, members, rank, tid);
+    for (int i = tid; i < members; i += NT)
+      if (rank[i] < (uint32_t)need) mark((int32_t)(uint32_t)list[i]);
+  } else {
+    int n2 = 1;
+    while (n2 < members) n2 <<= 1;
+    for (int i = members + tid; i < n2; i += NT) list[i] = ~0ull;
+    __syncthreads();
+    bitonic_sort(list, n2, tid, NT);
+    for (int t = tid; t < need; t += NT) mark((int32_t)(uint32_t)list[t]);
   }
+  for (int t = tid; t < C - need; t += NT) mark(cpos[t]);
   __syncthreads();
   // words [per * tid, per * tid + per) belong to thread tid
   const int per = (words + NT - 1) / NT;
@@ -314,38 +356,30 @@ __device__ bool memory_candidates(SelectShared<NW>& sh, Load4&& load4, int off, 
       },
       [](int) {});
   __syncthreads();
-  // the `need` smallest of the list (key descending, then position), then all C positions ascending:
-  // each entry's rank is the number of entries before it, counted by NT threads in shares
-  auto share = [&](int n, auto&& fn) __attribute__((always_inline)) {  // fn(entry, first, last) of a share
-    const int parts = max(1, NT / max(1, n));
-    for (int x = tid; x < parts * n; x += NT) fn(x % n, (x / n) * n / parts, (x / n + 1) * n / parts);
-  };
-  uint32_t* rank = h;          // the histogram is dead
+  // the `need` smallest of the list (key descending, then position), then all C positions ascending
+  uint32_t* rank = h;  // the histogram is dead
   uint32_t* pos = h + kListCap;
-  for (int i = tid; i < kListCap; i += NT) rank[i] = 0u;
-  __syncthreads();
-  share(members, [&](int i, int j0, int j1) __attribute__((always_inline)) {
-    const uint64_t own = list[i];
-    uint32_t n = 0;
-    for (int j = j0; j < j1; ++j) n += list[j] < own ? 1u : 0u;
-    if (n) atomicAdd(&rank[i], n);
+  auto sort_to = [&](auto* v, auto none, int n, auto&& put) __attribute__((always_inline)) {  // put(rank, entry)
+    if (n <= kRankMax) {
+      rank_entries<NT>(v, n, rank, tid);
+      for (int i = tid; i < n; i += NT) put((int)rank[i], v[i]);
+    } else {
+      int n2 = 1;
+      while (n2 < n) n2 <<= 1;
+      for (int i = n + tid; i < n2; i += NT) v[i] = none;
+      __syncthreads();
+      bitonic_sort(v, n2, tid, NT);
+      for (int i = tid; i < n; i += NT) put(i, v[i]);
+    }
+    __syncthreads();
+  };
+  static_assert(2 * kListCap <= kFastBins, "ranks and positions fit the histogram's space");
+  sort_to(list, ~0ull, members, [&](int r, uint64_t e) __attribute__((always_inline)) {
+    if (r < need) cpos[C - need + r] = (int32_t)(uint32_t)e;
   });
-  __syncthreads();
-  for (int i = tid; i < members; i += NT)
-    if (rank[i] < (uint32_t)need) cpos[C - need + (int)rank[i]] = (int32_t)(uint32_t)list[i];
-  __syncthreads();
-  for (int i = tid; i < kListCap; i += NT) rank[i] = 0u;
   for (int i = tid; i < C; i += NT) pos[i] = (uint32_t)cpos[i];
   __syncthreads();
-  share(C, [&](int i, int j0, int j1) __attribute__((always_inline)) {
-    const uint32_t own = pos[i];
-    uint32_t n = 0;
-    for (int j = j0; j < j1; ++j) n += pos[j] < own ? 1u : 0u;
-    if (n) atomicAdd(&rank[i], n);
-  });
-  __syncthreads();
-  for (int i = tid; i < C; i += NT) cpos[rank[i]] = (int32_t)pos[i];
-  __syncthreads();
+  sort_to(pos, ~0u, C, [&](int r, uint32_t e) __attribute__((always_inline)) { cpos[r] = (int32_t)e; });
   return true;
 }
 

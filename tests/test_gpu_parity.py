@@ -581,6 +581,18 @@ def test_cut_of_long_units_from_memory(d, lens, budget, density):
     _all_of(gpu_cases.run_gpu(wl, timed=True), None)
 
 
+@pytest.mark.parametrize("lens,budget,density", [([8191, 8193], 16, 0.02), ([12289, 33001], 110, 0.02),
+                                                 ([8257], 200, 0.002), ([20001, 9001], 16, 0.0)])
+def test_cut_of_staged_units(lens, budget, density):
+    """The cut's count of keys held in LDS, at and above the length from which keys below the first
+    4096's bound are skipped, with short and long lists of members (ranked by counting, sorted) and
+    (no planted keys: every score in one bin) too many for a list."""
+    import dataclasses
+    wl = _shape_workload(4, 2, 64, len(lens), 1, lens, budget=budget)
+    wl = dataclasses.replace(wl, layout=workloads.Layout(cluster_density=density) if density else workloads.Layout())
+    _all_of(gpu_cases.run_gpu(wl, timed=True), None)
+
+
 @pytest.mark.parametrize("sigma_rows", ["group_mean", "all_rows"])
 @pytest.mark.parametrize("h_q,h_kv,d,n_layers,lens,budget,cand_mult", [
     (32, 8, 128, 8, [40001], 16, 4), (8, 8, 64, 10, [30001], 8, 3), (16, 8, 64, 8, [36005], 30, 3)])
