@@ -85,8 +85,8 @@ def mfma_flops(wl) -> float:
 
 # sources that define each profiled kernel: its traffic record stays valid while they are unchanged
 KERNEL_SOURCES = {
-    "window_prune": ("stream_prune.hip", "select_gram.h", "compact_rows.h", "stream_passes.h",
-                     "stream_common.h", "common.h"),
+    "window_prune": ("stream_prune.hip", "stream_bounds.h", "select_gram.h", "compact_rows.h",
+                     "stream_passes.h", "stream_common.h", "common.h"),
     "window_stream": ("stream_window.hip", "stream_passes.h", "stream_common.h", "common.h"),
     "stats_stream": ("stream_stats.hip", "stream_passes.h", "stream_common.h", "common.h"),
     "mu_sigma_stream": ("stream_mu_sigma.hip", "stream_passes.h", "stream_common.h", "common.h"),
