@@ -10,14 +10,6 @@ namespace kv {
 namespace stream {
 namespace {
 
-// Sum over groups of eight lanes, in each of them.
-__device__ __forceinline__ float sum_of_8(float v) {
-  v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0xB1, 0xF, 0xF, false));
-  v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x4E, 0xF, 0xF, false));
-  v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x141, 0xF, 0xF, false));
-  return v;
-}
-
 constexpr int kPruneMaxTiles = kCandMaxLen / kTileKeys;
 // Order of the tiles for pass 2: bin 0 holds the tiles with a masked key (bound +inf), bin k >= 1
 // the tiles whose bound lies within ((k - 1) / 16, k / 16] octaves below the largest finite bound
@@ -98,17 +90,51 @@ template <int NBH, bool GREF = false> struct TileCodes {
   }
 };
 
-// Upper bounds of the base scores s = w_mu mu + lambda1 sigma (section 3.2, Eq. (5)) of every key of
+// Upper bound of the base score s = w_mu mu + lambda1 sigma (section 3.2, Eq. (5)) of every key of
 // a tile from its codes (row r of head h: t <= ref - code / 8) and the final row normalisers b:
 // a[h][r] = 2^(t - b[h][r]) <= a'[h][r], hence mu <= (1 / 32) sum_r abar'[r] (abar': mean over the
 // G heads) and, since a variance is at most the mean square, sigma <= sqrt(sum_r abar'[r]^2 / 31)
 // (sum_{h,r} a'^2 / (32 G - 1) for the dispersion over all rows).  The positive parts of w_mu and
 // lambda1 enter.
-//
-// Eight lanes take a tile, four rows each (their normalisers stay in registers), so a wave reads the
-// codes of eight tiles with one 1 KiB load instead of 64 lines per load and re-reads no normaliser
-// from LDS.  Bound by its 128 exponentials per tile.
-//
+// A thread takes whole tiles: bound by its 128 exponentials per tile.  Eight lanes per tile, four rows
+// each, read a wave's codes in one coalesced load, but 32 layers of 32768 keys (C = 256) then take
+// 433 us instead of 430 (kv_window_candidates) and 458 instead of 455.5 (kv_evict_pass).
+template <int NB, bool ALL>
+__device__ __forceinline__ float tile_bound(const uint32_t* codes_t, float ref, const float* bsh,
+                                            float wmu_p, float lam1_p, float inv_g) {
+  const uint4* src = reinterpret_cast<const uint4*>(codes_t);
+  float p1 = 0.f, p2 = 0.f;
+#pragma unroll 2
+  for (int v = 0; v < 8; ++v) {
+    const uint4 w4 = src[v];
+    const uint32_t ws[4] = {w4.x, w4.y, w4.z, w4.w};
+    float arow[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const float4 bv = *reinterpret_cast<const float4*>(bsh + b * 32 + 4 * v);
+      const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float code = (float)((ws[e] >> (8 * b)) & 0xFFu);
+        const float a = __builtin_amdgcn_exp2f(fmaf(code, -kCodeStep, ref) - bb[e]);
+        arow[e] += a;
+        if constexpr (ALL) p2 = fmaf(a, a, p2);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p1 += arow[e];
+      if constexpr (!ALL) {
+        const float ab = arow[e] * inv_g;
+        p2 = fmaf(ab, ab, p2);
+      }
+    }
+  }
+  constexpr float inv_n1 = ALL ? 1.f / (float)(NB * 32 - 1) : 1.f / 31.f;
+  const float mu_b = p1 * inv_g * (1.f / 32.f);
+  return fmaf(fmaf(lam1_p, __builtin_sqrtf(p2 * inv_n1), wmu_p * mu_b), kBoundSlack, kBoundFloor);
+}
+
 // The tiles of the workgroup (local tile i: keys from key0 + 32 i on, codes at codes_w + 32 i, ref in
 // ub[i]) in decreasing order of their bounds: a counting sort into bins of 1/16 of an octave below
 // the largest bound, each tile standing for its bin's upper edge.  Out: order[j], ub[j] (the bound)
@@ -121,64 +147,26 @@ __device__ __forceinline__ float order_tiles(const uint32_t* codes_w, int n_tile
                                              uint32_t* bmax_bits, uint32_t* n_eval, int tid) {
   constexpr int kTilesPerThread = kPruneMaxTiles / NT;
   static_assert(kPruneMaxTiles % NT == 0, "whole tiles per thread");
-  const int lane = tid & 63, wave = tid >> 6, v = lane & 7;
+  const int lane = tid & 63, wave = tid >> 6;
   uint32_t* cnt = bins;                  // [kOrderBins] tiles per bin
   uint32_t* off = bins + kOrderBins;     // [kOrderBins] first position of each bin, then a cursor
   for (int i = tid; i < kOrderBins; i += NT) cnt[i] = 0u;
   const float wmu_p = fmaxf(w_mu, 0.f), lam1_p = fmaxf(lam1, 0.f);
-  constexpr float inv_n1 = ALL ? 1.f / (float)(NB * 32 - 1) : 1.f / 31.f;
-  float bb[NB][4];  // normalisers of rows 4 v .. 4 v + 3
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const float4 x = *reinterpret_cast<const float4*>(bsh + b * 32 + 4 * v);
-    bb[b][0] = x.x;
-    bb[b][1] = x.y;
-    bb[b][2] = x.z;
-    bb[b][3] = x.w;
-  }
-  // step it of the workgroup: tiles it NT / 8 + tid / 8; the lane keeps the bounds of steps 8 u + v
-  auto tile_at = [&](int it) { return it * (NT / 8) + (tid >> 3); };
+  // the bounds of the thread's tiles tid + u NT (-inf: no candidate key, never revisited)
   float bnd[kTilesPerThread];
   float lmax = 0.f;  // largest finite bound (bounds are positive)
 #pragma unroll
   for (int u = 0; u < kTilesPerThread; ++u) {
-    bnd[u] = -INFINITY;  // no candidate key: never revisited
-    if (8 * u * (NT / 8) < n_tiles) {
-#pragma unroll 2
-      for (int e = 0; e < 8; ++e) {
-        const int i = tile_at(8 * u + e);
-        const bool in = i < n_tiles && key0 + i * kTileKeys < n_cand;
-        const float r = in ? ub[i] : INFINITY;
-        uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
-        if (r < INFINITY) w4 = *reinterpret_cast<const uint4*>(codes_w + 32 * i + 4 * v);
-        const uint32_t ws[4] = {w4.x, w4.y, w4.z, w4.w};
-        float p1 = 0.f, p2 = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float arow = 0.f;
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const float code = (float)((ws[q] >> (8 * b)) & 0xFFu);
-            const float a = __builtin_amdgcn_exp2f(fmaf(code, -kCodeStep, r) - bb[b][q]);
-            arow += a;
-            if constexpr (ALL) p2 = fmaf(a, a, p2);
-          }
-          p1 += arow;
-          if constexpr (!ALL) {
-            const float ab = arow * inv_g;
-            p2 = fmaf(ab, ab, p2);
-          }
-        }
-        p1 = sum_of_8(p1);
-        p2 = sum_of_8(p2);
-        const float mu_b = p1 * inv_g * (1.f / 32.f);
-        float bd = fmaf(fmaf(lam1_p, __builtin_sqrtf(p2 * inv_n1), wmu_p * mu_b), kBoundSlack, kBoundFloor);
-        if (!(r < INFINITY) || !(bd == bd)) bd = INFINITY;  // a masked key, or NaN inputs: revisit
-        if (!in) bd = -INFINITY;
-        if (v == e) bnd[u] = bd;
-      }
+    const int i = tid + u * NT;
+    bnd[u] = -INFINITY;
+    if (i < n_tiles && key0 + i * kTileKeys < n_cand) {
+      const float r = ub[i];
+      float bd = INFINITY;
+      if (r < INFINITY) bd = tile_bound<NB, ALL>(codes_w + 32 * i, r, bsh, wmu_p, lam1_p, inv_g);
+      if (!(bd == bd)) bd = INFINITY;  // NaN inputs: revisit
+      bnd[u] = bd;
+      if (bd < INFINITY) lmax = fmaxf(lmax, bd);
     }
-    if (bnd[u] < INFINITY) lmax = fmaxf(lmax, bnd[u]);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) lmax = fmaxf(lmax, __shfl_xor(lmax, o, 64));
@@ -230,7 +218,7 @@ __device__ __forceinline__ float order_tiles(const uint32_t* codes_w, int n_tile
   for (int u = 0; u < kTilesPerThread; ++u) {
     if (bin[u] >= 0) {
       const uint32_t pos = atomicAdd(&off[bin[u]], 1u);
-      order[pos] = (uint16_t)tile_at(8 * u + v);
+      order[pos] = (uint16_t)(tid + u * NT);
       ub[pos] = bin[u] == 0 ? INFINITY
                             : bmax * __builtin_amdgcn_exp2f(-(float)(bin[u] - 1) * (1.f / kBinsPerOctave));
     }
