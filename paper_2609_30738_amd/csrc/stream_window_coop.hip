@@ -30,8 +30,10 @@ __device__ __forceinline__ float2 load_partial(const float2* src) {
 }
 
 // In base-score mode (SC) pass 2 stores each key's base score instead of mu and sigma (see
-// stream_window.hip).
-template <int D, int NB, int W, bool ALL, int NW, int S, bool SC>
+// stream_window.hip).  MULTI: workgroups of several segments; those of one (per_wg is 1) are
+// compiled without the loop over segments (32 launches of one layer of 32768 keys each, 32 segments
+// of 1024 keys per unit: 1.52 -> 1.43 ms).
+template <int D, int NB, int W, bool ALL, int NW, int S, bool SC, bool MULTI>
 __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, uint32_t* arrive,
                                                                  uint32_t spin_limit) {
   using Gm = SGeo<D, NB>;
@@ -42,11 +44,11 @@ __global__ __launch_bounds__(NW * 64, 1) void window_coop_kernel(StreamArgs a, u
   __shared__ __align__(16) float bsh[R];
   __shared__ uint32_t all_arrived;
 
-  const int seg = blockIdx.x * a.per_wg, g = blockIdx.y, p = blockIdx.z;  // its first segment
+  const int seg = blockIdx.x * (MULTI ? a.per_wg : 1), g = blockIdx.y, p = blockIdx.z;  // its first segment
   const int L = a.lens[p];
   if ((int64_t)seg * a.seg_keys >= L) return;  // none of this unit's segments
   const int n_seg = (L + a.seg_keys - 1) / a.seg_keys;
-  const int seg_end = min(seg + a.per_wg, n_seg);  // one past its last
+  const int seg_end = MULTI ? min(seg + a.per_wg, n_seg) : seg + 1;  // one past its last
   const int k0 = seg * a.seg_keys;
   const int k1 = (int)min((int64_t)seg_end * a.seg_keys, (int64_t)L);
   const int G = a.h_q / a.h_kv;
@@ -177,14 +179,18 @@ __global__ void zero_words_kernel(uint32_t* w, int n) {
 // the chip at once (then no workgroup normally waits long); `launched` tells the caller whether it
 // ran.
 template <int D, int NB, int W> struct CoopLaunch {
-  template <bool ALL, bool SC> static const void* kernel() {
-    return reinterpret_cast<const void*>(window_coop_kernel<D, NB, W, ALL, kWaves, 2, SC>);
+  using Kernel = void (*)(StreamArgs, uint32_t*, uint32_t);
+  template <bool MULTI> static Kernel kernel(bool all, bool sc) {
+    if (all)
+      return sc ? window_coop_kernel<D, NB, W, true, kWaves, 2, true, MULTI>
+                : window_coop_kernel<D, NB, W, true, kWaves, 2, false, MULTI>;
+    return sc ? window_coop_kernel<D, NB, W, false, kWaves, 2, true, MULTI>
+              : window_coop_kernel<D, NB, W, false, kWaves, 2, false, MULTI>;
   }
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st, uint32_t* arrive,
                         uint32_t spin_limit, int64_t n_wgs, bool* launched) {
     const bool sc = args.score != nullptr;
-    const void* kern = args.sigma_all ? (sc ? kernel<true, true>() : kernel<true, false>())
-                                      : (sc ? kernel<false, true>() : kernel<false, false>());
+    const Kernel kern = args.per_wg > 1 ? kernel<true>(args.sigma_all, sc) : kernel<false>(args.sigma_all, sc);
     int dev = 0, n_cu = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -197,13 +203,7 @@ template <int D, int NB, int W> struct CoopLaunch {
     }
     const int n_units = s.n_prob * s.h_kv;
     zero_words_kernel<<<(n_units + 255) / 256, 256, 0, st>>>(arrive, n_units);
-    if (args.sigma_all) {
-      if (sc) window_coop_kernel<D, NB, W, true, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-      else window_coop_kernel<D, NB, W, true, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-    } else {
-      if (sc) window_coop_kernel<D, NB, W, false, kWaves, 2, true><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-      else window_coop_kernel<D, NB, W, false, kWaves, 2, false><<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
-    }
+    kern<<<grid, kThreads, 0, st>>>(args, arrive, spin_limit);
     e = hipGetLastError();
     *launched = e == hipSuccess;
     return e;
