@@ -122,7 +122,8 @@ kv::StreamPlan stream_plan_of(const kv_problem* pr, const kv::Shape& s) {
 // 405 us as two workgroups each through base scores, 310 whole).  Where every second tile can hold
 // a candidate they do not (112 units of 8000 keys, C = 256: 190 and 226 us).
 kv::StreamPlan cand_plan_of(const kv_problem* pr, const kv::Shape& s, int max_cand) {
-  return kv::stream_plan(s, pr->len_host, s.max_len / 32 >= 2 * max_cand);
+  return kv::stream_plan(s, pr->len_host,
+                         s.max_len / 32 >= 2 * max_cand ? kv::WgRule::kWhole : kv::WgRule::kEven);
 }
 
 // Workspace of the window entry points: the larger of the chunked and the streaming layouts.
@@ -307,7 +308,8 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   float* score = reinterpret_cast<float*>(base + head);
   const size_t score_bytes = align_up((size_t)token_extent(pr) * pr->h_kv * sizeof(float));
   char* rest = base + head + score_bytes;  // kv_window_base_scores' workspace: window part, mu, sigma
-  const kv::StreamPlan plan = kv::stream_shape_ok(s, scale) ? stream_plan_of(pr, s) : kv::StreamPlan{};
+  const kv::StreamPlan plan =
+      kv::stream_shape_ok(s, scale) ? kv::stream_plan(s, pr->len_host, kv::WgRule::kAny) : kv::StreamPlan{};
   const size_t win = window_ws_bytes(pr, s);
   if (kv::stream_shape_ok(s, scale) && s.w == 32 && cand_mult > 0 && kv::prune_segs_ok(plan, stride) &&
       kv::prune_segs_bytes(s) <= base_scores_ws_bytes(pr, s, false) - win) {

@@ -58,7 +58,7 @@ hipError_t launch_window_passes(const Shape& s, const void* q_win, const void* k
 // window row live in the workspace, [n_units][max_segs][32 row_blocks()] float2.
 // A workgroup takes `per_wg` consecutive segments of a unit (statistics are still merged segment by
 // segment, so the results do not depend on it): one where the segments fit the chip at once, else
-// as many as it takes to fit; max_wgs workgroups for the longest unit, n_wgs over the batch.
+// as many as the rule allows; max_wgs workgroups for the longest unit, n_wgs over the batch.
 struct StreamPlan {
   int seg_keys;
   int max_segs;
@@ -69,8 +69,13 @@ struct StreamPlan {
   bool one_wg() const { return max_wgs == 1 && per_wg <= kStreamMaxPerWg; }
 };
 bool stream_shape_ok(const Shape& s, float scale);
-// whole: a whole unit to a workgroup where it can hold the statistics of its segments
-StreamPlan stream_plan(const Shape& s, const int32_t* lens_host, bool whole = false);
+// Segments of a workgroup where there are more than fit the chip at once.
+enum class WgRule {
+  kEven,   // both passes in full: two, or one (and two launches) where that does not fit
+  kAny,    // a second pass that revisits few tiles: as many as it takes to fit
+  kWhole,  // the candidate kernel: the whole unit where a workgroup can hold its statistics
+};
+StreamPlan stream_plan(const Shape& s, const int32_t* lens_host, WgRule rule = WgRule::kEven);
 size_t stream_ws_bytes(const Shape& s, const StreamPlan& plan);
 size_t stream_counter_offset(const Shape& s, const StreamPlan& plan);  // counters after the partials
 // Pass 1: segment partials into ws or, with ws == nullptr (only when plan.max_segs == 1), the

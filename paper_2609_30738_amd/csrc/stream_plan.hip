@@ -11,9 +11,39 @@ bool stream_shape_ok(const Shape& s, float scale) {
   return s.dtype == kDtBf16 && window && (s.d == 64 || s.d == 128) && scale > 0.f;
 }
 
-StreamPlan stream_plan(const Shape& s, const int32_t* lens, bool whole) {
-  // about one segment per compute unit (256 on MI355X), whole 256-key steps of the eight waves
-  constexpr int64_t kTarget = 256, kStep = stream::kWaves * stream::kTileKeys;
+namespace {
+
+constexpr int64_t kCus = 256, kXcds = 8;                            // MI355X
+constexpr int64_t kStep = stream::kWaves * stream::kTileKeys;       // keys of a step of the eight waves
+constexpr int64_t kMaxScheduled = 1024;                             // workgroups that `scheduled_within` follows
+
+// Whether no CU streams more than `limit` keys when every workgroup takes `keys` keys of a unit, one
+// workgroup to a CU (the key rings fill its LDS).  Workgroup i of a launch goes to XCD i mod 8, the
+// grid's empty workgroups (ragged units) counted, and there to the CU that is free first: units of one
+// or two workgroups that are mostly of one fill every second XCD only.
+bool scheduled_within(const Shape& s, const int32_t* lens, int64_t keys, int64_t limit) {
+  constexpr int kPer = kCus / kXcds;
+  const int64_t wgs = (s.max_len + keys - 1) / keys;
+  int32_t busy[kXcds][kPer] = {};  // keys of each CU, at most limit (2^25)
+  int64_t id = 0;
+  for (int p = 0; p < s.n_prob; ++p)
+    for (int g = 0; g < s.h_kv; ++g, id += wgs)
+      for (int64_t w = 0; w * keys < lens[p]; ++w) {
+        int32_t* cus = busy[(id + w) % kXcds];
+        int32_t least = cus[0];
+        for (int c = 1; c < kPer; ++c) least = std::min(least, cus[c]);
+        const int64_t sum = least + std::min(keys, lens[p] - w * keys);
+        if (sum > limit) return false;
+        int c = 0;
+        while (cus[c] != least) ++c;
+        cus[c] = (int32_t)sum;
+      }
+  return true;
+}
+
+}  // namespace
+
+StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
   const int64_t max_seg = ((int64_t)s.max_len + kStep - 1) / kStep * kStep;
   int64_t total = 0;
   for (int p = 0; p < s.n_prob; ++p) total += (int64_t)s.h_kv * lens[p];
@@ -22,7 +52,20 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, bool whole) {
     for (int p = 0; p < s.n_prob; ++p) n += s.h_kv * ((lens[p] + keys - 1) / keys);
     return n;
   };
-  int64_t seg = ((total + kTarget - 1) / kTarget + kStep - 1) / kStep * kStep;
+  // about one segment per compute unit, whole steps
+  int64_t seg = ((total + kCus - 1) / kCus + kStep - 1) / kStep * kStep;
+  // Segments over the chip's CUs: one launch of longer ones (or of workgroups of several) ends when
+  // its busiest CU does, the segments' own two launches take about two rounds.  A CU streams alone
+  // hardly faster than beside 255 others (33 GB/s against 27), so past two segments' keys on one CU
+  // two launches are shorter.  mu and sigma of 36 ragged batches (w = 32, d = 128, G = 4): one launch
+  // 1.0 to 1.58 times as fast where that holds (0.95 at the least), 0.54 to 1.07 where it does not
+  // (one in five 1.36); a prompt of 100001 keys beside 30 of 1000 took 815 us in one launch and 151 in
+  // two, 24 prompts of 2429 to 30424 keys 549 and 420, 20 layers of 14000 keys 257 and 366.
+  // (Of many workgroups to a CU only the longest is looked at.)
+  auto one_launch = [&](int64_t keys) {
+    if (std::min<int64_t>(keys, s.max_len) > 2 * seg) return false;
+    return work_items(keys) > kMaxScheduled || scheduled_within(s, lens, keys, 2 * seg);
+  };
   if (s.w == 32) {
     // four tiles per wave at least: shorter segments cost more in exchanges than they save
     seg = std::min(std::max<int64_t>(1024, seg), max_seg);
@@ -33,15 +76,22 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, bool whole) {
     // the chip's CUs would cost a second round: then longer segments (160 units of 2500 keys whole
     // 37 us, as 320 segments 58)
     seg = std::min(std::max<int64_t>(s.max_len <= 1024 ? 1024 : kStep, seg), max_seg);
-    while (seg < max_seg && work_items(seg) > kTarget)
-      seg = std::min(max_seg, seg + std::max<int64_t>(kStep, seg / 16 / kStep * kStep));
+    int64_t longer = seg;
+    while (longer < max_seg && work_items(longer) > kCus)
+      longer = std::min(max_seg, longer + std::max<int64_t>(kStep, longer / 16 / kStep * kStep));
+    if (longer > seg && one_launch(longer)) seg = longer;
   }
   StreamPlan plan;
   plan.seg_keys = (int)seg;
   plan.max_segs = (int)(((int64_t)s.max_len + seg - 1) / seg);
-  // segments over the chip's CUs go to workgroups of several, as few as it takes to fit
-  plan.per_wg = whole && plan.max_segs <= kStreamMaxPerWg ? plan.max_segs : 1;
-  while (plan.per_wg < plan.max_segs && work_items(seg * plan.per_wg) > kTarget) ++plan.per_wg;
+  int64_t per_wg = 1;
+  if (rule == WgRule::kWhole && plan.max_segs <= kStreamMaxPerWg) {
+    per_wg = plan.max_segs;
+  } else {
+    while (per_wg < plan.max_segs && work_items(seg * per_wg) > kCus) ++per_wg;
+    if (per_wg > 1 && rule != WgRule::kAny && !one_launch(seg * per_wg)) per_wg = 1;
+  }
+  plan.per_wg = (int)per_wg;
   plan.max_wgs = (plan.max_segs + plan.per_wg - 1) / plan.per_wg;
   plan.n_wgs = work_items(seg * plan.per_wg);
   return plan;
