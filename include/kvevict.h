@@ -180,18 +180,20 @@ int kv_window_mu_sigma_ex(const kv_problem* pr, const void* q_win, const void* k
  * bit for bit what kv_window_mu_sigma_ex's mu and sigma give, without those two arrays.  score has
  * the layout of mu (problem p at tok_off[p]*h_kv, [h_kv][L_p], fp32, 16-byte aligned).
  * lambda1: [n_prob] fp32 device.  w_mu: finite (1 for the paper's score).
- * For bf16 batches (w = 32 with G in {1, 2, 4}, or w in {8, 16} with G w <= 64; d in {64, 128},
- * scale > 0) the scores are formed
- * inside the window kernel's second pass, which then writes one array instead of two; with every
- * (problem, kv head) scored by one workgroup no workspace is needed.  Otherwise, and when the
- * one-launch path cannot run, mu and sigma go through the workspace
- * (kv_base_scores_workspace_bytes).  Calls that overlap on one workspace race. */
+ * The scores are formed inside the window kernel's second pass, which then writes one array instead
+ * of two; bf16 batches (w = 32 with G in {1, 2, 4}, or w in {8, 16} with G w <= 64; d in {64, 128},
+ * scale > 0) with every (problem, kv head) scored by one workgroup need no workspace.  Only where
+ * such a batch takes several workgroups to a (problem, kv head) and these do not fit the chip at once
+ * do mu and sigma go through the workspace (kv_base_scores_workspace_bytes).  Calls that overlap on
+ * one workspace race. */
 int kv_window_base_scores(const kv_problem* pr, const void* q_win, const void* k, float scale,
                           const float* lambda1, float w_mu, int32_t sigma_rows, float* row_max,
                           float* row_sum, float* score, void* ws, size_t ws_bytes, void* stream);
 
-/* Bytes of device workspace kv_window_base_scores needs for this batch with scale > 0 (0 if none;
- * 256-byte alignment).  Returns 0 for invalid arguments as well. */
+/* Bytes of device workspace kv_window_base_scores needs for this batch (0 if none; 256-byte
+ * alignment).  Enough for every scale, but for bf16 batches of w = 32 whose (problem, kv head) units
+ * are one segment each (at most about 1 / 256 of the batch's keys): there 0, for scale > 0, and
+ * scale <= 0 needs kv_workspace_bytes.  Returns 0 for invalid arguments as well. */
 size_t kv_base_scores_workspace_bytes(const kv_problem* pr);
 
 /* Greedy diversity-aware selection (Eq. (2), (4), (5); section 3.2), per problem p and kv head g:
@@ -304,7 +306,9 @@ int kv_window_candidates(const kv_problem* pr, const void* q_win, const void* k,
                          float* row_max, float* row_sum, void* ws, size_t ws_bytes, void* stream);
 
 /* Bytes of device workspace kv_window_candidates needs for this batch and these selection
- * arguments with scale > 0 (256-byte alignment).  Returns 0 for invalid arguments. */
+ * arguments (256-byte alignment): for every scale, but for the batches of one segment to a unit that
+ * kv_base_scores_workspace_bytes names (cand_mult > 0, L_p <= 32768) for scale > 0 only.  Returns 0
+ * for invalid arguments. */
 size_t kv_candidates_workspace_bytes(const kv_problem* pr, int32_t budget, int32_t cand_mult,
                                      int32_t keep_tail, const kv_select_opts* opts);
 

@@ -148,12 +148,20 @@ bool scores_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale
   return kv::stream_shape_ok(s, scale) && stream_plan_of(pr, s).one_wg();
 }
 
-// Workspace of kv_window_base_scores: none for the fused path (with fused_ok, for a positive
-// scale), else the window paths' part and rows of mu and sigma.
-size_t base_scores_ws_bytes(const kv_problem* pr, const kv::Shape& s, bool fused_ok = true) {
-  if (fused_ok && scores_in_window_pass(pr, s, 1.f)) return 0;
+// Workspace of kv_window_base_scores with this scale: none where the window kernel's second pass forms
+// the scores of whole units; the chunked kernels (every shape with scale <= 0 among them) form them in
+// their second pass too and need the window paths' part; else that part and rows of mu and sigma.
+size_t base_scores_ws_bytes(const kv_problem* pr, const kv::Shape& s, float scale) {
+  if (!kv::stream_shape_ok(s, scale)) return window_ws_bytes(pr, s);
+  if (stream_plan_of(pr, s).one_wg()) return 0;
   const size_t keys = (size_t)token_extent(pr) * pr->h_kv;
   return window_ws_bytes(pr, s) + 2 * align_up(keys * sizeof(float));
+}
+
+// Batches of w = 32 whose units are one segment each: their queries answer for scale > 0 only, the
+// others for every scale.
+bool one_segment_units(const kv_problem* pr, const kv::Shape& s) {
+  return s.w == 32 && kv::stream_shape_ok(s, 1.f) && stream_plan_of(pr, s).max_segs == 1;
 }
 
 // Candidate lists of kv_window_candidates: one list of `stride` 8-byte entries per (problem, kv
@@ -174,12 +182,12 @@ bool cands_in_window_pass(const kv_problem* pr, const kv::Shape& s, float scale,
 // Workspace of kv_window_candidates: the lists and the units' normalisers, then with the fused
 // path the tile codes of its first pass, without it the scores and what kv_window_base_scores needs
 // after them.
-size_t cand_ws_bytes(const kv_problem* pr, const kv::Shape& s, int stride, bool fused) {
+size_t cand_ws_bytes(const kv_problem* pr, const kv::Shape& s, int stride, float scale, bool fused) {
   const size_t head = cand_lists_bytes(pr, stride) + align_up((size_t)pr->n_prob * pr->h_kv * sizeof(float));
   if (fused)
     return head + align_up((size_t)pr->n_prob * pr->h_kv * kv::cand_code_stride(s) * sizeof(uint32_t));
   return head + align_up((size_t)token_extent(pr) * pr->h_kv * sizeof(float)) +
-         base_scores_ws_bytes(pr, s, false);
+         base_scores_ws_bytes(pr, s, scale);
 }
 
 // Selection, and with k_out / v_out the compaction of the selected rows, in one launch; base
@@ -287,7 +295,7 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
   if (stride > kv::select_max_candidates(pr->d, elem_bytes(pr->dtype))) return KV_ERR_SHAPE;
   const bool fused = cands_in_window_pass(pr, s, scale, cand_mult, stride);
-  const size_t need = cand_ws_bytes(pr, s, stride, fused);
+  const size_t need = cand_ws_bytes(pr, s, stride, scale, fused);
   if (ws_bytes < need || !ws || (reinterpret_cast<uintptr_t>(ws) & (kWsAlign - 1)))
     return KV_ERR_WORKSPACE;
   const bool all = sigma_rows == KV_SIGMA_ALL_ROWS;
@@ -312,7 +320,7 @@ int window_candidates_impl(const kv_problem* pr, const void* q_win, const void* 
       kv::stream_shape_ok(s, scale) ? kv::stream_plan(s, pr->len_host, kv::WgRule::kAny) : kv::StreamPlan{};
   const size_t win = window_ws_bytes(pr, s);
   if (kv::stream_shape_ok(s, scale) && s.w == 32 && cand_mult > 0 && kv::prune_segs_ok(plan, stride) &&
-      kv::prune_segs_bytes(s) <= base_scores_ws_bytes(pr, s, false) - win) {
+      win + kv::prune_segs_bytes(s) <= base_scores_ws_bytes(pr, s, scale)) {
     // only the scores that can reach the cut (the codes take the place of mu and sigma)
     st = launch_status(kv::launch_prune_segs(s, plan, q_win, k, scale, lambda1, w_mu, budget, b_dev, cand_mult,
                                              keep_tail, rest, rest + win, row_max, row_sum, score, all, hs));
@@ -491,7 +499,8 @@ int kv_window_mu_sigma_noalloc(const kv_problem* pr, const void* q_win, const vo
 size_t kv_base_scores_workspace_bytes(const kv_problem* pr) {
   kv::Shape s;
   if (check_problem(pr, &s) != KV_OK) return 0;
-  return base_scores_ws_bytes(pr, s);
+  const size_t need = base_scores_ws_bytes(pr, s, 1.f);
+  return one_segment_units(pr, s) ? need : std::max(need, base_scores_ws_bytes(pr, s, -1.f));
 }
 
 int kv_window_base_scores(const kv_problem* pr, const void* q_win, const void* k, float scale,
@@ -505,7 +514,7 @@ int kv_window_base_scores(const kv_problem* pr, const void* q_win, const void* k
   if (!std::isfinite(scale) || !std::isfinite(w_mu)) return KV_ERR_ARG;
   if (sigma_rows != KV_SIGMA_GROUP_MEAN && sigma_rows != KV_SIGMA_ALL_ROWS) return KV_ERR_ARG;
   const bool fused = scores_in_window_pass(pr, s, scale);
-  const size_t need = fused ? 0 : base_scores_ws_bytes(pr, s, false);
+  const size_t need = base_scores_ws_bytes(pr, s, scale);
   if (need > 0 && (ws_bytes < need || !ws || (reinterpret_cast<uintptr_t>(ws) & (kWsAlign - 1))))
     return KV_ERR_WORKSPACE;
   const bool all = sigma_rows == KV_SIGMA_ALL_ROWS;
@@ -600,7 +609,9 @@ size_t kv_candidates_workspace_bytes(const kv_problem* pr, int32_t budget, int32
   if (opts && opts->pool != 1) return 0;
   const int stride = max_candidates(pr, budget, cand_mult, keep_tail, b_host);
   if (stride > kv::select_max_candidates(pr->d, elem_bytes(pr->dtype))) return 0;
-  return cand_ws_bytes(pr, s, stride, cands_in_window_pass(pr, s, 1.f, cand_mult, stride));
+  const bool fused = cands_in_window_pass(pr, s, 1.f, cand_mult, stride);
+  const size_t need = cand_ws_bytes(pr, s, stride, 1.f, fused);
+  return fused && one_segment_units(pr, s) ? need : std::max(need, cand_ws_bytes(pr, s, stride, -1.f, false));
 }
 
 int kv_window_candidates(const kv_problem* pr, const void* q_win, const void* k, float scale,

@@ -351,6 +351,35 @@ def test_base_scores_checks():
     assert call(ws=NULL, ws_bytes=need) == _lib.KV_ERR_WORKSPACE
 
 
+SCALE_CASES = [
+    dict(w=8, lens=(300,)), dict(w=16, h_q=16, lens=(5000, 700)), dict(w=8, lens=(15600,) * 32),
+    dict(w=8, h_q=8, lens=(2500,) * 20),
+    dict(lens=(5000,) * 24), dict(lens=(14000,) * 20), dict(lens=(30000,) * 14), dict(lens=(4096,)),
+    dict(lens=(100001,) * 8), dict(lens=(31000,) * 10 + (9000,) * 10), dict(w=20, h_q=16, lens=(900,)),
+    dict(h_q=24, lens=(20000,)), dict(dtype=_lib.KV_F32, lens=(4096,) * 8)]
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the calls would launch")
+@pytest.mark.parametrize("kw", SCALE_CASES, ids=lambda kw: "-".join(str(v) for v in kw.values())[:40])
+@pytest.mark.parametrize("scale", [0.088, 0.0, -0.088])
+def test_queried_workspace_is_accepted_for_every_scale(kw, scale):
+    """A workspace of the size that the query gives passes validation whatever the scale's sign (the
+    queries do not see it; scale <= 0 takes the chunked kernels): without a GPU the launch itself is
+    what fails.  (Batches of w = 32 with one segment to a unit answer for scale > 0 only.)"""
+    lib, pr = _lib.lib(), HostProblem(**kw)
+    ws = ctypes.c_void_p(256)  # aligned, never dereferenced
+    need = lib.kv_base_scores_workspace_bytes(pr.ref())
+    assert lib.kv_window_base_scores(pr.ref(), P, P, scale, P, 1.0, 0, P, P, P, ws if need else NULL, need,
+                                     NULL) == _lib.KV_ERR_LAUNCH
+    need = lib.kv_candidates_workspace_bytes(pr.ref(), 64, 4, pr.s.w, None)
+    assert lib.kv_window_candidates(pr.ref(), P, P, scale, P, 0, 64, 4, pr.s.w, None, P, P, ws, need,
+                                    NULL) == _lib.KV_ERR_LAUNCH
+    assert lib.kv_evict_pass(pr.ref(), P, P, P, scale, P, P, 0, 64, 4, pr.s.w, None, P, P, P, NULL, P, P, ws,
+                             need, NULL) == _lib.KV_ERR_LAUNCH
+    need = lib.kv_workspace_bytes(pr.ref(), 64, 4, pr.s.w)
+    assert lib.kv_window_mu_sigma(pr.ref(), P, P, scale, P, P, P, P, ws, need, NULL) == _lib.KV_ERR_LAUNCH
+
+
 def test_select_scored_checks():
     """kv_mmr_select_scored validates like kv_mmr_select_ex, with the scores in place of mu /
     sigma / lambda1, and k_out / v_out both or neither."""

@@ -605,3 +605,30 @@ def test_units_of_several_workgroups_revisit_few_tiles(h_q, h_kv, d, n_layers, l
     wl = _shape_workload(h_q, h_kv, d, len(lens), n_layers, lens, budget=budget)
     assert lens[0] * 64 // 256 // 32 >= 3 * cand_mult * budget  # tiles of a workgroup against C
     _all_of(gpu_cases.run_gpu(wl, timed=True, cand_mult=cand_mult, sigma_rows=sigma_rows), [0, wl.n_prob - 1])
+
+
+@pytest.mark.parametrize("w,h_q,lens", [(8, 32, [1000, 531]), (16, 16, [5003]), (32, 32, [5000] * 24)])
+def test_scores_with_a_negative_scale(w, h_q, lens):
+    """-scale with negated queries has the logits of scale and q bit for bit, but takes the chunked
+    kernels where scale > 0 streams: row statistics and scores differ by the order of their sums only,
+    of up to 128 rows and 5003 keys (relative error below 2e-5), in a workspace of the queried size."""
+    import torch
+    from paper_2609_30738_amd import _lib
+    print(f"[gpu case] negative scale w={w} h_q={h_q} lens={lens[:3]} x{len(lens)}", flush=True)
+    b = _lib.Batch("bf16", h_q, 8, 128, w, lens)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q = torch.randn(len(lens) * h_q * w * 128, device="cuda", generator=gen).to(torch.bfloat16)
+    k = torch.randn(sum(lens) * 8 * 128, device="cuda", generator=gen).to(torch.bfloat16)
+    lam = torch.full((len(lens),), 0.3, device="cuda")
+    outs = []
+    for sign in (1.0, -1.0):
+        need = _lib.base_scores_workspace_bytes(b)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+        rm, rs = (torch.zeros(len(lens) * h_q * w, device="cuda") for _ in range(2))
+        score = torch.zeros(sum(lens) * 8, device="cuda")
+        _lib.window_base_scores(b, (sign * q).contiguous(), k, sign * 0.088, lam, rm, rs, score, ws=ws)
+        torch.cuda.synchronize()
+        outs.append([x.cpu().numpy().astype(np.float64) for x in (rm, rs, score)])
+    for a, c in zip(*outs):
+        assert np.all(np.abs(a) > 0) and np.max(np.abs(a - c) / np.abs(a)) < 2e-5
