@@ -126,10 +126,14 @@ kv::StreamPlan cand_plan_of(const kv_problem* pr, const kv::Shape& s, int max_ca
                          s.max_len / 32 >= 2 * max_cand ? kv::WgRule::kWhole : kv::WgRule::kEven);
 }
 
-// Workspace of the window entry points: the larger of the chunked and the streaming layouts.
+// Workspace of the window entry points: the larger of the chunked and the streaming layouts.  Units of
+// one segment use no partials; at w = 32 they have always been counted.
 size_t window_ws_bytes(const kv_problem* pr, const kv::Shape& s) {
   size_t b = kv::window_stats_ws_bytes(s);
-  if (kv::stream_shape_ok(s, 1.f)) b = std::max(b, kv::stream_ws_bytes(s, stream_plan_of(pr, s)));
+  if (kv::stream_shape_ok(s, 1.f)) {
+    const kv::StreamPlan plan = stream_plan_of(pr, s);
+    if (s.w == 32 || plan.max_segs > 1) b = std::max(b, kv::stream_ws_bytes(s, plan));
+  }
   return align_up(b);
 }
 

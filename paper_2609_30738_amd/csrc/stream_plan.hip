@@ -80,6 +80,11 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
     while (longer < max_seg && work_items(longer) > kCus)
       longer = std::min(max_seg, longer + std::max<int64_t>(kStep, longer / 16 / kStep * kStep));
     if (longer > seg && one_launch(longer)) seg = longer;
+    // what the chunked kernels do within the static scratch is not refused for the partials' size
+    // (a thousand short units beside a long one in segments under 1024 keys)
+    const size_t most = std::max(window_stats_ws_bytes(s), kNoAllocScratchBytes);
+    while (seg < max_seg && stream_ws_bytes(s, {(int)seg, (int)((s.max_len + seg - 1) / seg)}) > most)
+      seg = std::min(max_seg, 2 * seg);
   }
   StreamPlan plan;
   plan.seg_keys = (int)seg;

@@ -351,6 +351,23 @@ def test_base_scores_checks():
     assert call(ws=NULL, ws_bytes=need) == _lib.KV_ERR_WORKSPACE
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the calls would launch")
+@pytest.mark.parametrize("kw", [
+    dict(h_q=8, h_kv=8, w=8, lens=(300,) * 8192), dict(h_q=2, h_kv=1, w=16, lens=(1024,) * 65535),
+    dict(h_q=8, h_kv=1, w=8, lens=(20000,) + (50,) * 1000), dict(h_q=4, h_kv=1, w=16, lens=(33000,) + (20,) * 900),
+    dict(h_q=32, w=8, lens=(4096,)), dict(h_q=16, w=16, lens=(5003, 300) * 8)])
+def test_no_alloc_entry_takes_short_windows_that_fit_in_chunks(kw):
+    """Windows of 8 and 16 rows whose chunk partials (8 bytes per window row, padded to blocks of 32,
+    and 1024 keys) fit the static scratch are not refused for it: validation passes, the launch is what
+    fails without a GPU."""
+    lib, pr = _lib.lib(), HostProblem(**kw)
+    rows = kw["h_q"] // pr.s.h_kv * kw["w"]
+    chunks = pr.s.h_kv * len(kw["lens"]) * -(-max(kw["lens"]) // 1024)
+    assert chunks * -(-rows // 32) * 32 * 8 <= _lib.KV_NOALLOC_SCRATCH_BYTES
+    assert lib.kv_workspace_bytes(pr.ref(), 64, 4, 8) <= _lib.KV_NOALLOC_SCRATCH_BYTES
+    assert lib.kv_window_mu_sigma_noalloc(pr.ref(), P, P, 0.088, 0, P, P, P, P, NULL) == _lib.KV_ERR_LAUNCH
+
+
 SCALE_CASES = [
     dict(w=8, lens=(300,)), dict(w=16, h_q=16, lens=(5000, 700)), dict(w=8, lens=(15600,) * 32),
     dict(w=8, h_q=8, lens=(2500,) * 20),
