@@ -79,7 +79,10 @@ __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
         mx = fmax3(fmax3(mx, d[7], d[8]), d[9], d[10]);
         mx = fmax3(fmax3(mx, d[11], d[12]), d[13], d[14]);
         tmax[b] = __builtin_elementwise_maximum(mx, d[15]);
-        const float mn = __builtin_elementwise_maximum(m_run[b], tmax[b] * c);
+        float mn = __builtin_elementwise_maximum(m_run[b], tmax[b] * c);
+        const float m_new = mn;
+        // W < 32: a lane whose logits so far are all -inf keeps (-inf, 0), as in the chunked kernels
+        if constexpr (W < 32) mn = mn == -INFINITY ? 0.f : mn;
         const float keep = __builtin_amdgcn_exp2f(m_run[b] - mn);  // 0 on the lane's first tile
         float ex[16];
 #pragma unroll
@@ -88,7 +91,7 @@ __device__ __forceinline__ void stats_tiles(const KeyStream<D, NB, NW, S>& ks,
 #pragma unroll
         for (int u = 0; u < 4; ++u) zs[u] = (ex[4 * u] + ex[4 * u + 1]) + (ex[4 * u + 2] + ex[4 * u + 3]);
         z_run[b] = fmaf(z_run[b], keep, (zs[0] + zs[1]) + (zs[2] + zs[3]));
-        m_run[b] = mn;
+        m_run[b] = m_new;
       }
       hook.template interior<NB>(ks.tile_index(j), tmax);
     } else {

@@ -632,3 +632,53 @@ def test_scores_with_a_negative_scale(w, h_q, lens):
         outs.append([x.cpu().numpy().astype(np.float64) for x in (rm, rs, score)])
     for a, c in zip(*outs):
         assert np.all(np.abs(a) > 0) and np.max(np.abs(a - c) / np.abs(a)) < 2e-5
+
+
+@pytest.mark.parametrize("w,h_q,d", [(8, 32, 128), (8, 16, 64), (16, 16, 128), (16, 8, 64)])
+@pytest.mark.parametrize("lens", [[700], [5003, 1500]])
+def test_short_windows_with_logits_of_minus_infinity(w, h_q, d, lens):
+    """Keys 0 .. 599 (every wave's first tiles) whose products overflow to a logit of -inf for every
+    window row: they weigh nothing, and the statistics are those of the other keys (64-bit reference;
+    2e-5 for the fp32 sums over at most 5003 keys and 64 rows)."""
+    import torch
+    from paper_2609_30738_amd import _lib
+    print(f"[gpu case] -inf logits w={w} h_q={h_q} d={d} lens={lens}", flush=True)
+    b = _lib.Batch("bf16", h_q, 8, d, w, lens)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    G, P, scale = h_q // 8, len(lens), d ** -0.5
+    q = torch.randn(P, 8, G, w, d, device="cuda", generator=gen)
+    q[..., 0] = 2.0 ** 10
+    q = q.to(torch.bfloat16)
+    ks = []
+    for L in lens:
+        k = torch.randn(8, L, d, device="cuda", generator=gen)
+        k[..., 0] = 0.0
+        k[:, :600, 0] = -2.0 ** 125
+        ks.append(k.to(torch.bfloat16))
+    f = dict(dtype=torch.float32, device="cuda")
+    out = {n: torch.empty(P * h_q * w, **f) for n in ("row_max", "row_sum")}
+    out.update({n: torch.empty(sum(lens) * 8, **f) for n in ("mu", "sigma")})
+    ws = torch.empty(_lib.workspace_bytes(b, 1), dtype=torch.uint8, device="cuda")
+    kk = torch.cat([k.reshape(-1) for k in ks])
+    _lib.window_mu_sigma(b, q, kk, scale, out["row_max"], out["row_sum"], out["mu"], out["sigma"], ws)
+    rm2, rs2 = torch.empty(P * h_q * w, **f), torch.empty(P * h_q * w, **f)
+    _lib.window_scores(b, q, kk, scale, rm2, rs2, ws)
+    torch.cuda.synchronize()
+    ref = {n: [] for n in out}
+    for p, L in enumerate(lens):
+        lg = scale * torch.matmul(q[p].double().cpu()[..., 1:].reshape(8, G * w, d - 1),
+                                  ks[p].double().cpu()[..., 1:].transpose(1, 2).contiguous()).reshape(8, G, w, L)
+        lg[..., :600] = -float("inf")
+        lg.masked_fill_(torch.arange(L) > (L - w + torch.arange(w))[:, None], -float("inf"))
+        m = lg.max(-1, keepdim=True).values
+        e = (lg - m).exp()
+        ref["row_max"].append(m.reshape(-1))
+        ref["row_sum"].append(e.sum(-1).reshape(-1))
+        a = (e / e.sum(-1, keepdim=True)).mean(1)
+        ref["mu"].append(a.mean(1).reshape(-1))
+        ref["sigma"].append(a.std(1).reshape(-1))
+    for n, got in (*out.items(), ("row_max", rm2), ("row_sum", rs2)):
+        r, g = torch.cat(ref[n]), got.double().cpu()
+        bad = (g - r).abs() > 2e-5 * r.abs()
+        assert not bool(bad.any()) and bool(torch.isfinite(g).all()), (n, int(bad.sum()), float((g - r).abs().max()))
