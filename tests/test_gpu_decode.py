@@ -185,3 +185,23 @@ def test_decode_over_the_compacted_cache_of_the_pass():
         err = np.abs(o[g * G:(g + 1) * G] - ref)
         assert np.all(err <= 2e-5 * vmax + 1e-5 * np.abs(ref)), f"g={g}: {err.max():.3g}"
     assert same >= wl.h_kv - 1, f"only {same} kv heads admitted the oracle's rows"
+
+
+@pytest.mark.parametrize("dtype,d,h_q", [("bf16", 128, 32), ("bf16", 64, 8), ("f32", 128, 8), ("f32", 64, 64)])
+def test_decode_of_values_near_the_largest_float(dtype, d, h_q):
+    """Values of 2^118 in every row and logits 7 octaves higher from row 200 on: the weighted sums stay
+    finite because no weight exceeds 1 (301 rows of 2^118 sum to less than 2^127), and the output is 2^118."""
+    lens = [300, 260]
+    di = workloads.draw_decode(dtype, h_q, 8, d, 301, lens, seed=4)
+    q = evict.decode(di.q, dtype)
+    u = q[:, ::h_q // 8]  # one head of each group
+    rows = np.zeros(di.k.shape, dtype=np.float32)
+    rows[:, :, 200:] = (7 * np.log(2) / (di.scale * np.sum(u * u, -1, keepdims=True)) * u)[:, :, None]
+    v = np.full(di.v.shape, 2.0 ** 118, dtype=np.float32)
+    bits = workloads.f32_to_bf16_bits if dtype == "bf16" else np.asarray
+    di.k[:], di.v[:] = bits(rows), bits(v)
+    for append in (False, True):
+        if append:
+            di.v_new[:] = bits(np.full(di.v_new.shape, 2.0 ** 118, dtype=np.float32))
+        out, _, _ = _run(di, append, "large values")
+        np.testing.assert_allclose(out, 2.0 ** 118, rtol=1e-5)
