@@ -734,7 +734,7 @@ int check_cache_batch(const kv_cache_batch* cb) {
 kv::DecodePlan decode_plan_of(const kv_cache_batch* cb) {
   int max_len = 0;
   for (int p = 0; p < cb->n_prob; ++p) max_len = std::max(max_len, (int)cb->len_host[p]);
-  return kv::decode_plan(cb->n_prob, cb->h_kv, max_len);
+  return kv::decode_plan(cb->n_prob, cb->h_kv, max_len, cb->h_q / cb->h_kv, cb->d * elem_bytes(cb->dtype));
 }
 
 }  // namespace

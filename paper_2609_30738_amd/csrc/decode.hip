@@ -367,20 +367,25 @@ hipError_t decode_dispatch(const DecodeArgs& a, int n_prob, hipStream_t st) {
 
 }  // namespace
 
-DecodePlan decode_plan(int n_prob, int h_kv, int max_len) {
-  // Up to kOneSplit rows a unit stays whole: 300 rows of 64 units take 12.0 us whole and 12.8 us
-  // split and merged, 500 rows of 8 units 15.8 and 12.8 us.  Long caches get about three rounds of
+DecodePlan decode_plan(int n_prob, int h_kv, int max_len, int group, int row_bytes) {
+  // Up to one_split rows a unit stays whole, a launch less: 300 rows of 64 units (G = 4, d = 128, bf16)
+  // take 12.0 us whole and 12.8 us split and merged, 500 rows of 8 units 15.8 and 12.8 us.  A row costs
+  // about its bytes times the heads: where these are at most kLightRow, 500 rows of 8 to 256 units take
+  // 9.6 to 13.5 us whole and 11.9 to 15.4 split (G = 1 at 128 to 512 bytes a row, G = 2 at 128 and 256,
+  // G = 4 at 128); G = 4 at 256 bytes (d = 64, fp32) 13.2 to 16.3 and 11.9 to 15.9.  Long caches get about three rounds of
   // the 768 workgroups that fit the chip at once (three per CU), so that caches of unequal length
   // even out (768 workgroups 717 us, 1536 703, 2304 706, 6144 729 at 256 units of 32768 rows);
   // where that leaves fewer than 1024 rows to a split, one round of splits of at least kMinSplit
   // rows (2000 rows of 8 units: 11.4 us, at least 256 rows 12.6 us).
-  constexpr int64_t kOneSplit = 384, kMinSplit = 128, kStep = 64, kRound = 768;
+  constexpr int64_t kMinSplit = 128, kStep = 64, kRound = 768;
+  constexpr int kLightRow = 512;
+  const int64_t one_split = group * row_bytes <= kLightRow ? 512 : 384;
   static_assert(3 * kRound <= kMaxSplits, "the merge holds every split's weight");
   const int64_t units = (int64_t)n_prob * h_kv;
   const int64_t rows = (int64_t)max_len + 1;  // room for an appended row
   auto splits = [&](int64_t groups) { return std::max<int64_t>(1, groups / units); };
   int64_t n_split = 1;
-  if (rows > kOneSplit) {
+  if (rows > one_split) {
     n_split = splits(3 * kRound);
     if (rows < 1024 * n_split) n_split = std::min(splits(kRound), (rows + kMinSplit - 1) / kMinSplit);
   }

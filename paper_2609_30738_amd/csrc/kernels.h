@@ -228,7 +228,8 @@ struct DecodeArgs {
 struct DecodePlan {
   int n_split, split_rows;
 };
-DecodePlan decode_plan(int n_prob, int h_kv, int max_len);
+// group: query heads of a kv head; row_bytes: of a K row
+DecodePlan decode_plan(int n_prob, int h_kv, int max_len, int group, int row_bytes);
 size_t decode_ws_bytes(int n_prob, int h_q, int d, const DecodePlan& plan);
 hipError_t launch_decode(int dtype, int d, int n_prob, const DecodeArgs& a, hipStream_t stream);
 

@@ -252,6 +252,17 @@ def test_decode_checks():
     assert call(big, ws=NULL, ws_bytes=need) == _lib.KV_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("dtype,h_q,h_kv,d,whole", [
+    (_lib.KV_BF16, 8, 8, 64, 511), (_lib.KV_BF16, 16, 8, 128, 511), (_lib.KV_BF16, 32, 8, 64, 511),
+    (_lib.KV_F32, 8, 8, 128, 511), (_lib.KV_BF16, 32, 8, 128, 383), (_lib.KV_F32, 32, 8, 64, 383)])
+def test_decode_keeps_short_caches_whole(dtype, h_q, h_kv, d, whole):
+    """Caches of up to `whole` rows (and an appended one) are not split, so need no workspace: longer
+    ones of light rows (group times row bytes at most 512) than of others."""
+    for rows, split in ((1, False), (whole, False), (whole + 1, True)):
+        cb, keep = _cache_batch(dtype=dtype, h_q=h_q, h_kv=h_kv, d=d, stride=600, lens=(rows, 1))
+        assert (_lib.lib().kv_decode_workspace_bytes(ctypes.byref(cb)) > 0) == split, rows
+
+
 def test_compact_block_size_check():
     pr = HostProblem()
     assert _lib.lib().kv_compact_cache_ex(pr.ref(), P, P, P, 64, 32, NULL, NULL, 95, P, P,
