@@ -368,7 +368,8 @@ typedef struct kv_cache_batch {
 } kv_cache_batch;
 
 /* Bytes of device workspace kv_decode_attention needs for this batch (0 if none; 256-byte
- * alignment).  Returns 0 for invalid arguments as well. */
+ * alignment): enough for the same problems at any shorter lengths too.  Returns 0 for invalid
+ * arguments as well. */
 size_t kv_decode_workspace_bytes(const kv_cache_batch* cb);
 
 /* Attention of one generated token per problem over its cache (section 4.3: after eviction the

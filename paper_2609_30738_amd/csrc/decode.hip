@@ -389,18 +389,19 @@ DecodePlan decode_plan(int n_prob, int h_kv, int max_len, int group, int row_byt
     n_split = splits(3 * kRound);
     if (rows < 1024 * n_split) n_split = std::min(splits(kRound), (rows + kMinSplit - 1) / kMinSplit);
   }
+  DecodePlan plan;
+  plan.ws_splits = (int)n_split;
   int64_t split_rows = (rows + n_split - 1) / n_split;
   split_rows = (split_rows + kStep - 1) / kStep * kStep;
   n_split = (rows + split_rows - 1) / split_rows;
-  DecodePlan plan;
   plan.n_split = (int)n_split;
   plan.split_rows = (int)split_rows;
   return plan;
 }
 
 size_t decode_ws_bytes(int n_prob, int h_q, int d, const DecodePlan& plan) {
-  if (plan.n_split == 1) return 0;
-  return (size_t)n_prob * h_q * plan.n_split * (d + 2) * sizeof(float);
+  if (plan.ws_splits == 1) return 0;
+  return (size_t)n_prob * h_q * plan.ws_splits * (d + 2) * sizeof(float);
 }
 
 hipError_t launch_decode(int dtype, int d, int n_prob, const DecodeArgs& a, hipStream_t stream) {

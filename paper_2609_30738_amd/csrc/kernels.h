@@ -225,8 +225,10 @@ struct DecodeArgs {
   float* out;         // [n_prob][h_q][d]
   float* part;        // [n_prob][h_q][n_split][d + 2] when n_split > 1
 };
+// ws_splits: the splits that the workspace is sized for, at least n_split and never fewer for a longer
+// cache (whole 64-row steps make n_split itself fall now and then as a cache grows).
 struct DecodePlan {
-  int n_split, split_rows;
+  int n_split, split_rows, ws_splits;
 };
 // group: query heads of a kv head; row_bytes: of a K row
 DecodePlan decode_plan(int n_prob, int h_kv, int max_len, int group, int row_bytes);

@@ -263,6 +263,20 @@ def test_decode_keeps_short_caches_whole(dtype, h_q, h_kv, d, whole):
         assert (_lib.lib().kv_decode_workspace_bytes(ctypes.byref(cb)) > 0) == split, rows
 
 
+@pytest.mark.parametrize("dtype,h_q,d,n_prob", [(_lib.KV_BF16, 32, 128, 1), (_lib.KV_BF16, 32, 128, 2),
+                                                (_lib.KV_F32, 8, 64, 3), (_lib.KV_BF16, 64, 64, 16)])
+def test_decode_workspace_of_a_longer_cache_suffices(dtype, h_q, d, n_prob):
+    """The need never falls as a cache grows (13000 and 300000 rows among others), so a workspace sized
+    for the longest length serves every step before it."""
+    last = 0
+    for rows in [*range(1, 13100, 7), *range(13100, 300000, 1009)]:
+        cb, keep = _cache_batch(dtype=dtype, h_q=h_q, d=d, stride=300001, lens=(rows,) * n_prob)
+        need = _lib.lib().kv_decode_workspace_bytes(ctypes.byref(cb))
+        assert need >= last, rows
+        last = need
+    assert last > 0
+
+
 def test_compact_block_size_check():
     pr = HostProblem()
     assert _lib.lib().kv_compact_cache_ex(pr.ref(), P, P, P, 64, 32, NULL, NULL, 95, P, P,
