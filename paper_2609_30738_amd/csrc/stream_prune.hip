@@ -195,8 +195,8 @@ __global__ __launch_bounds__(NW * 64, 1) void window_prune_kernel(StreamArgs a) 
   };
   if constexpr (!PRUNE) {
     // the scores of every candidate key: copied, counted and their maximum taken by all waves, four
-    // loads of a thread in flight
-    for (int i0 = tid; i0 < n_ord * kTileKeys; i0 += 4 * NT) {
+    // loads of a thread in flight (the last half-wave without keys stays for the histogram's ballots)
+    for (int i0 = tid; i0 < (n_ord * kTileKeys + 63) / 64 * 64; i0 += 4 * NT) {
       float sv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) sv[u] = i0 + u * NT < n_cand ? load_score(i0 + u * NT) : 0.f;
