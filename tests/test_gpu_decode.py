@@ -205,3 +205,49 @@ def test_decode_of_values_near_the_largest_float(dtype, d, h_q):
             di.v_new[:] = bits(np.full(di.v_new.shape, 2.0 ** 118, dtype=np.float32))
         out, _, _ = _run(di, append, "large values")
         np.testing.assert_allclose(out, 2.0 ** 118, rtol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,d,h_q,n_prob,rows,splits", [
+    ("bf16", 128, 32, 32, 9300, 9), ("bf16", 64, 8, 32, 9300, 9), ("f32", 64, 16, 32, 9300, 9),
+    ("f32", 128, 8, 32, 9300, 9), ("bf16", 128, 64, 4, 33000, 24)])
+@pytest.mark.parametrize("append", [False, True])
+def test_decode_over_caches_larger_than_the_chip(dtype, d, h_q, n_prob, rows, splits, append):
+    """K and V of 256 MiB and more (read past the caches), unequal lengths, in about three rounds of
+    splits (256 units of at least 1024 rows a split) and in one: the longest, the shortest and a few
+    other problems against the oracle."""
+    import torch
+    h_kv, stride = 8, rows + 1
+    assert 2 * n_prob * h_kv * rows * d * (2 if dtype == "bf16" else 4) >= 256 << 20
+    lens = [rows - 97 * p if p % 5 else rows - 31 * p for p in range(n_prob - 1)] + [1]
+    print(f"[gpu case] decode past the caches dtype={dtype} h_q={h_q} d={d} lens={lens[:3]}.. "
+          f"x{n_prob} append={append}", flush=True)
+    cb = _lib.CacheBatch(dtype, h_q, h_kv, d, stride, lens)
+    need = n_prob * h_q * splits * (d + 2) * 4
+    assert _lib.decode_workspace_bytes(cb) == -(-need // 256) * 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).to(dt)
+    q, k, v = rnd(n_prob, h_q, d), rnd(n_prob, h_kv, stride, d), rnd(n_prob, h_kv, stride, d)
+    k[:, :, ::1000] *= 4  # a few dominant rows
+    kn, vn = (rnd(n_prob, h_kv, d), rnd(n_prob, h_kv, d)) if append else (None, None)
+    out = torch.empty(n_prob * h_q * d, dtype=torch.float32, device="cuda")
+    ws = torch.empty(_lib.decode_workspace_bytes(cb), dtype=torch.uint8, device="cuda")
+    k0, v0 = k.clone(), v.clone()
+    _lib.decode_attention(cb, q, k, v, kn, vn, d ** -0.5, out, ws)
+    torch.cuda.synchronize()
+    o = out.cpu().numpy().reshape(n_prob, h_q, d)
+    host = lambda x: x.float().cpu().numpy().astype(np.float64)
+    for p in (0, 1, n_prob // 2, n_prob - 1):
+        L = lens[p]
+        kd, vd = host(k0[p, :, :L]), host(v0[p, :, :L])
+        ref = decode.decode_attention(host(q[p]), kd, vd, d ** -0.5, host(kn[p]) if append else None,
+                                      host(vn[p]) if append else None)
+        vmax = max(np.abs(vd).max(), np.abs(host(vn[p])).max() if append else 0.0)
+        err = np.abs(o[p] - ref)
+        assert np.all(err <= 2e-5 * vmax + 1e-5 * np.abs(ref)), f"p={p} L={L}: worst error {err.max():.3g}"
+    if append:  # row L of every block is the new token's, nothing else changed
+        at = torch.tensor(lens, device="cuda")
+        i = torch.arange(n_prob, device="cuda")
+        k0[i, :, at], v0[i, :, at] = kn, vn
+    assert torch.equal(k, k0) and torch.equal(v, v0)

@@ -634,6 +634,55 @@ def test_scores_with_a_negative_scale(w, h_q, lens):
         assert np.all(np.abs(a) > 0) and np.max(np.abs(a - c) / np.abs(a)) < 2e-5
 
 
+def _check_window_statistics(dtype, q, ks, w, rtol, hidden=0, sigma_rows="group_mean"):
+    """kv_window_mu_sigma_ex, kv_window_scores and kv_window_base_scores of queries q [P, h_kv, G, w, d]
+    and keys ks (one [h_kv, L, d] per problem) against 64-bit statistics; the first `hidden` keys count
+    as logits of -inf (their first elements make them so)."""
+    import torch
+    from paper_2609_30738_amd import _lib
+    P, h_kv, G, _, d = q.shape
+    lens, scale = [k.shape[1] for k in ks], d ** -0.5
+    b = _lib.Batch(dtype, h_kv * G, h_kv, d, w, lens)
+    f = dict(dtype=torch.float32, device="cuda")
+    out = {n: torch.empty(P * h_kv * G * w, **f) for n in ("row_max", "row_sum")}
+    out.update({n: torch.empty(sum(lens) * h_kv, **f) for n in ("mu", "sigma")})
+    ws = torch.empty(_lib.workspace_bytes(b, 1), dtype=torch.uint8, device="cuda")
+    kk = torch.cat([k.reshape(-1) for k in ks])
+    _lib.window_mu_sigma_ex(b, q, kk, scale, sigma_rows, out["row_max"], out["row_sum"], out["mu"], out["sigma"], ws)
+    rm2, rs2, rm3, rs3 = (torch.empty(P * h_kv * G * w, **f) for _ in range(4))
+    score = torch.empty_like(out["mu"])
+    need = _lib.base_scores_workspace_bytes(b)
+    ws_sc = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    _lib.window_scores(b, q, kk, scale, rm2, rs2, ws)
+    _lib.window_base_scores(b, q, kk, scale, torch.full((P,), 0.25, device="cuda"), rm3, rs3, score,
+                            sigma_rows=sigma_rows, ws=ws_sc)
+    torch.cuda.synchronize()
+    ref = {n: [] for n in out}
+    h0 = 1 if hidden else 0  # the element that hides keys is 0 in the others
+    for p, L in enumerate(lens):
+        lg = scale * torch.matmul(q[p].double().cpu()[..., h0:].reshape(h_kv, G * w, d - h0),
+                                  ks[p].double().cpu()[..., h0:].transpose(1, 2).contiguous())
+        lg = lg.reshape(h_kv, G, w, L)
+        lg[..., :hidden] = -float("inf")
+        lg.masked_fill_(torch.arange(L) > (L - w + torch.arange(w))[:, None], -float("inf"))
+        m = lg.max(-1, keepdim=True).values
+        e = (lg - m).exp()
+        z = e.sum(-1, keepdim=True)
+        e = e / z
+        ref["row_max"].append(m.reshape(-1))
+        ref["row_sum"].append(z.reshape(-1))
+        a = e.mean(1)
+        ref["mu"].append(a.mean(1).reshape(-1))
+        ref["sigma"].append((a.std(1) if sigma_rows == "group_mean" else e.reshape(h_kv, G * w, L).std(1)).reshape(-1))
+    for n, got in (*out.items(), ("row_max", rm2), ("row_sum", rs2), ("row_max", rm3), ("row_sum", rs3)):
+        r, g = torch.cat(ref[n]), got.double().cpu()
+        bad = (g - r).abs() > rtol * r.abs() + (1e-5 if n == "row_max" else 0.0)
+        assert not bool(bad.any()) and bool(torch.isfinite(g).all()), (n, int(bad.sum()), float((g - r).abs().max()))
+    # the score is fma(lambda1, sigma, mu) of the same mu and sigma, one rounding
+    s64 = 0.25 * out["sigma"].double() + out["mu"].double()
+    assert bool(((score.double() - s64).abs() <= 2.0 ** -24 * s64.abs()).all())
+
+
 @pytest.mark.parametrize("w,h_q,d", [(8, 32, 128), (8, 16, 64), (16, 16, 128), (16, 8, 64)])
 @pytest.mark.parametrize("lens", [[700], [5003, 1500]])
 def test_short_windows_with_logits_of_minus_infinity(w, h_q, d, lens):
@@ -641,44 +690,46 @@ def test_short_windows_with_logits_of_minus_infinity(w, h_q, d, lens):
     window row: they weigh nothing, and the statistics are those of the other keys (64-bit reference;
     2e-5 for the fp32 sums over at most 5003 keys and 64 rows)."""
     import torch
-    from paper_2609_30738_amd import _lib
     print(f"[gpu case] -inf logits w={w} h_q={h_q} d={d} lens={lens}", flush=True)
-    b = _lib.Batch("bf16", h_q, 8, d, w, lens)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(7)
-    G, P, scale = h_q // 8, len(lens), d ** -0.5
-    q = torch.randn(P, 8, G, w, d, device="cuda", generator=gen)
+    q = torch.randn(len(lens), 8, h_q // 8, w, d, device="cuda", generator=gen)
     q[..., 0] = 2.0 ** 10
-    q = q.to(torch.bfloat16)
     ks = []
     for L in lens:
         k = torch.randn(8, L, d, device="cuda", generator=gen)
         k[..., 0] = 0.0
         k[:, :600, 0] = -2.0 ** 125
         ks.append(k.to(torch.bfloat16))
-    f = dict(dtype=torch.float32, device="cuda")
-    out = {n: torch.empty(P * h_q * w, **f) for n in ("row_max", "row_sum")}
-    out.update({n: torch.empty(sum(lens) * 8, **f) for n in ("mu", "sigma")})
-    ws = torch.empty(_lib.workspace_bytes(b, 1), dtype=torch.uint8, device="cuda")
-    kk = torch.cat([k.reshape(-1) for k in ks])
-    _lib.window_mu_sigma(b, q, kk, scale, out["row_max"], out["row_sum"], out["mu"], out["sigma"], ws)
-    rm2, rs2 = torch.empty(P * h_q * w, **f), torch.empty(P * h_q * w, **f)
-    _lib.window_scores(b, q, kk, scale, rm2, rs2, ws)
-    torch.cuda.synchronize()
-    ref = {n: [] for n in out}
-    for p, L in enumerate(lens):
-        lg = scale * torch.matmul(q[p].double().cpu()[..., 1:].reshape(8, G * w, d - 1),
-                                  ks[p].double().cpu()[..., 1:].transpose(1, 2).contiguous()).reshape(8, G, w, L)
-        lg[..., :600] = -float("inf")
-        lg.masked_fill_(torch.arange(L) > (L - w + torch.arange(w))[:, None], -float("inf"))
-        m = lg.max(-1, keepdim=True).values
-        e = (lg - m).exp()
-        ref["row_max"].append(m.reshape(-1))
-        ref["row_sum"].append(e.sum(-1).reshape(-1))
-        a = (e / e.sum(-1, keepdim=True)).mean(1)
-        ref["mu"].append(a.mean(1).reshape(-1))
-        ref["sigma"].append(a.std(1).reshape(-1))
-    for n, got in (*out.items(), ("row_max", rm2), ("row_sum", rs2)):
-        r, g = torch.cat(ref[n]), got.double().cpu()
-        bad = (g - r).abs() > 2e-5 * r.abs()
-        assert not bool(bad.any()) and bool(torch.isfinite(g).all()), (n, int(bad.sum()), float((g - r).abs().max()))
+    _check_window_statistics("bf16", q.to(torch.bfloat16), ks, w, 2e-5, hidden=600)
+
+
+@pytest.mark.parametrize("sigma_rows", ["group_mean", "all_rows"])
+@pytest.mark.parametrize("h_kv,d,lens", [(2, 64, [20000, 333]), (8, 128, [4096] * 8), (8, 64, [17000, 16500])])
+def test_chunked_four_row_blocks(h_kv, d, lens, sigma_rows):
+    """Four fp32 heads of 32 rows in the chunked kernels: more than 16 chunks with every row block a
+    workgroup of its own (44 chunks), and workgroups of all four blocks, with the row statistics merged in
+    the second pass (256 chunks of 4 to a unit) and by the combine kernel (272 chunks, 17 to a unit).
+    Logits of random keys stay below 7, whose fp32 error of about 7 d^(1/2) 2^-24 = 5e-6 averages out in
+    the sums: 1e-5."""
+    import torch
+    print(f"[gpu case] chunked, four row blocks h_kv={h_kv} d={d} lens={lens} {sigma_rows}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    q = torch.randn(len(lens), h_kv, 4, 32, d, device="cuda", generator=gen)
+    ks = [torch.randn(h_kv, L, d, device="cuda", generator=gen) for L in lens]
+    _check_window_statistics("f32", q, ks, 32, 1e-5, sigma_rows=sigma_rows)
+
+
+@pytest.mark.parametrize("sigma_rows", ["group_mean", "all_rows"])
+def test_units_of_several_workgroups_ragged(sigma_rows):
+    """Units of six, three and one workgroups in one batch of the two-launch candidate path, two segments
+    of 6144 keys to a workgroup: workgroups past the end of short units, units with no more positions than
+    candidates (68 and 128), and a last workgroup whose 20 keys all lie in the kept tail."""
+    lens, n_layers, budget = [61460, 33001, 300, 100], 2, 32
+    wl = _shape_workload(32, 8, 128, len(lens), n_layers, lens, budget=budget)
+    seg = -(-(-(-sum(lens) * n_layers * 8 // 256)) // 256) * 256
+    assert seg == 6144 and 2 * seg // 32 >= 3 * 4 * budget  # tiles of a workgroup against C
+    assert sum(8 * n_layers * -(-L // seg) for L in lens) > 256 and 0 < lens[0] % (2 * seg) <= wl.w
+    run = gpu_cases.run_gpu(wl, timed=True, sigma_rows=sigma_rows)
+    print("  ", gpu_cases.summarize(gpu_cases.check_all(run, js=[0, 3, 5, 6], heads=[0, 5])), flush=True)
