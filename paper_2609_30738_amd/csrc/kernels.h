@@ -65,6 +65,11 @@ struct StreamPlan {
   int per_wg;
   int max_wgs;
   int64_t n_wgs;
+  bool ragged;  // some units have fewer segments than the longest
+  // Columns of a grid of n workgroups to the longest unit: odd where units have empty ones.
+  // Workgroups go to the 8 XCDs in turn, so an even number starts every unit of one workgroup on the
+  // same few of them.
+  int columns(int n) const { return ragged ? n | 1 : n; }
   // every unit's keys in one workgroup, which can hold the statistics of per_wg segments
   bool one_wg() const { return max_wgs == 1 && per_wg <= kStreamMaxPerWg; }
 };

@@ -57,6 +57,7 @@ struct StreamArgs {
   float c;  // softmax scale * log2(e)
   int seg_keys, max_segs;
   int per_wg;  // consecutive segments of a workgroup (the kernels that run both passes)
+  int seg_columns, wg_columns;  // grid columns of a launch by segments, by workgroups
   float2* part;           // [n_units][max_segs][R] segment partials (m, z), base 2; pass 1 with
                           // part == nullptr (one segment per unit) writes row_max_out / row_sum_out
   const float* row_max;   // pass 2 from given statistics (part == nullptr)
@@ -306,6 +307,8 @@ inline StreamArgs base_args(const Shape& s, const StreamPlan& plan, const void* 
   a.seg_keys = plan.seg_keys;
   a.max_segs = plan.max_segs;
   a.per_wg = plan.per_wg;
+  a.seg_columns = plan.columns(plan.max_segs);
+  a.wg_columns = plan.columns(plan.max_wgs);
   return a;
 }
 

@@ -93,7 +93,7 @@ template <int D, int NB, int W> struct MuSigmaLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
     // eight waves (two per SIMD), two-tile rings (measured: one wave per SIMD with four-tile rings
     // runs this pass 20 % slower)
-    const dim3 grid(args.max_segs, s.h_kv, s.n_prob);
+    const dim3 grid(args.seg_columns, s.h_kv, s.n_prob);
     if (args.sigma_all) mu_sigma_stream_kernel<D, NB, W, true, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
     else mu_sigma_stream_kernel<D, NB, W, false, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
     return hipGetLastError();

@@ -19,15 +19,13 @@ constexpr int64_t kMaxScheduled = 1024;                             // workgroup
 
 // Whether no CU streams more than `limit` keys when every workgroup takes `keys` keys of a unit, one
 // workgroup to a CU (the key rings fill its LDS).  Workgroup i of a launch goes to XCD i mod 8, the
-// grid's empty workgroups (ragged units) counted, and there to the CU that is free first: units of one
-// or two workgroups that are mostly of one fill every second XCD only.
-bool scheduled_within(const Shape& s, const int32_t* lens, int64_t keys, int64_t limit) {
+// grid's empty workgroups (`columns` to a unit) counted, and there to the CU that is free first.
+bool scheduled_within(const Shape& s, const int32_t* lens, int64_t keys, int columns, int64_t limit) {
   constexpr int kPer = kCus / kXcds;
-  const int64_t wgs = (s.max_len + keys - 1) / keys;
   int32_t busy[kXcds][kPer] = {};  // keys of each CU, at most limit (2^25)
   int64_t id = 0;
   for (int p = 0; p < s.n_prob; ++p)
-    for (int g = 0; g < s.h_kv; ++g, id += wgs)
+    for (int g = 0; g < s.h_kv; ++g, id += columns)
       for (int64_t w = 0; w * keys < lens[p]; ++w) {
         int32_t* cus = busy[(id + w) % kXcds];
         int32_t least = cus[0];
@@ -57,14 +55,23 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
   // Segments over the chip's CUs: one launch of longer ones (or of workgroups of several) ends when
   // its busiest CU does, the segments' own two launches take about two rounds.  A CU streams alone
   // hardly faster than beside 255 others (33 GB/s against 27), so past two segments' keys on one CU
-  // two launches are shorter.  mu and sigma of 36 ragged batches (w = 32, d = 128, G = 4): one launch
-  // 1.0 to 1.58 times as fast where that holds (0.95 at the least), 0.54 to 1.07 where it does not
-  // (one in five 1.36); a prompt of 100001 keys beside 30 of 1000 took 815 us in one launch and 151 in
-  // two, 24 prompts of 2429 to 30424 keys 549 and 420, 20 layers of 14000 keys 257 and 366.
-  // (Of many workgroups to a CU only the longest is looked at.)
-  auto one_launch = [&](int64_t keys) {
-    if (std::min<int64_t>(keys, s.max_len) > 2 * seg) return false;
-    return work_items(keys) > kMaxScheduled || scheduled_within(s, lens, keys, 2 * seg);
+  // two launches are shorter.  Over 60 batches of unequal lengths (d = 128, G = 4) mu and sigma take
+  // 0.33 to 1.08 times as long as in two launches always at w = 32, 0.84 in the median, and 0.27 to 1.08
+  // times the chunked kernels' time at w = 8 (0.77).  In one launch always, a prompt of 100001 keys
+  // beside 30 of 1000 took 815 us (w = 32) and 495 (w = 8), now 149 and 105; in two launches always,
+  // 20 layers of 14000 keys 366 us, in one 257.
+  StreamPlan plan;
+  auto set_segments = [&](int64_t keys) {
+    plan.seg_keys = (int)keys;
+    plan.max_segs = (int)((s.max_len + keys - 1) / keys);
+    plan.ragged = (int64_t)s.n_prob * s.h_kv * plan.max_segs > work_items(keys);
+  };
+  // the plan's segments, `per` to a workgroup, against segments of `even` keys
+  auto one_launch = [&](int64_t per, int64_t even) {
+    const int64_t keys = per * plan.seg_keys;
+    if (std::min<int64_t>(keys, s.max_len) > 2 * even) return false;
+    return work_items(keys) > kMaxScheduled ||
+           scheduled_within(s, lens, keys, plan.columns((int)((s.max_len + keys - 1) / keys)), 2 * even);
   };
   if (s.w == 32) {
     // four tiles per wave at least: shorter segments cost more in exchanges than they save
@@ -79,22 +86,21 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
     int64_t longer = seg;
     while (longer < max_seg && work_items(longer) > kCus)
       longer = std::min(max_seg, longer + std::max<int64_t>(kStep, longer / 16 / kStep * kStep));
-    if (longer > seg && one_launch(longer)) seg = longer;
+    set_segments(longer);
+    if (longer > seg && one_launch(1, seg)) seg = longer;
     // what the chunked kernels do within the static scratch is not refused for the partials' size
     // (a thousand short units beside a long one in segments under 1024 keys)
     const size_t most = std::max(window_stats_ws_bytes(s), kNoAllocScratchBytes);
-    while (seg < max_seg && stream_ws_bytes(s, {(int)seg, (int)((s.max_len + seg - 1) / seg)}) > most)
+    for (set_segments(seg); seg < max_seg && stream_ws_bytes(s, plan) > most; set_segments(seg))
       seg = std::min(max_seg, 2 * seg);
   }
-  StreamPlan plan;
-  plan.seg_keys = (int)seg;
-  plan.max_segs = (int)(((int64_t)s.max_len + seg - 1) / seg);
+  set_segments(seg);
   int64_t per_wg = 1;
   if (rule == WgRule::kWhole && plan.max_segs <= kStreamMaxPerWg) {
     per_wg = plan.max_segs;
   } else {
     while (per_wg < plan.max_segs && work_items(seg * per_wg) > kCus) ++per_wg;
-    if (per_wg > 1 && rule != WgRule::kAny && !one_launch(seg * per_wg)) per_wg = 1;
+    if (per_wg > 1 && rule != WgRule::kAny && !one_launch(per_wg, seg)) per_wg = 1;
   }
   plan.per_wg = (int)per_wg;
   plan.max_wgs = (plan.max_segs + plan.per_wg - 1) / plan.per_wg;

@@ -152,14 +152,14 @@ __global__ __launch_bounds__(NW * 64, 1) void prune_segs_kernel(StreamArgs a, Se
 }
 
 template <int D, int NB, int W> struct PruneSegsLaunch {
-  static hipError_t run(const Shape& s, const StreamArgs& a, hipStream_t st, SegArgs sa, int max_wgs) {
+  static hipError_t run(const Shape& s, const StreamArgs& a, hipStream_t st, SegArgs sa) {
     if constexpr (W != 32) {
       return hipErrorInvalidValue;  // the tile codes hold 32 window rows
     } else {
-      stats_codes_kernel<D, NB, kWaves, 2><<<dim3(a.max_segs, s.h_kv, s.n_prob), kThreads, 0, st>>>(a, sa);
+      stats_codes_kernel<D, NB, kWaves, 2><<<dim3(a.seg_columns, s.h_kv, s.n_prob), kThreads, 0, st>>>(a, sa);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      const dim3 grid(max_wgs, s.h_kv, s.n_prob);
+      const dim3 grid(a.wg_columns, s.h_kv, s.n_prob);
       if (a.sigma_all) prune_segs_kernel<D, NB, true, kWaves, 2><<<grid, kThreads, 0, st>>>(a, sa);
       else prune_segs_kernel<D, NB, false, kWaves, 2><<<grid, kThreads, 0, st>>>(a, sa);
       return hipGetLastError();
@@ -210,7 +210,7 @@ hipError_t launch_prune_segs(const Shape& s, const StreamPlan& plan, const void*
   a.codes = static_cast<uint32_t*>(codes_ws);
   a.code_stride = 32 * tiles;
   const stream::SegArgs sa{reinterpret_cast<float*>(a.codes + (size_t)s.n_prob * s.h_kv * a.code_stride), tiles};
-  return stream::launch_for_shape<stream::PruneSegsLaunch>(s, a, stream, sa, plan.max_wgs);
+  return stream::launch_for_shape<stream::PruneSegsLaunch>(s, a, stream, sa);
 }
 
 }  // namespace kv

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(NW * 64, 1) void stats_stream_kernel(StreamArgs a) 
 
 template <int D, int NB, int W> struct StatsLaunch {
   static hipError_t run(const Shape& s, const StreamArgs& args, hipStream_t st) {
-    const dim3 grid(args.max_segs, s.h_kv, s.n_prob);
+    const dim3 grid(args.seg_columns, s.h_kv, s.n_prob);
     stats_stream_kernel<D, NB, W, kWaves, 2><<<grid, kThreads, 0, st>>>(args);
     return hipGetLastError();
   }

@@ -196,7 +196,7 @@ template <int D, int NB, int W> struct CoopLaunch {
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kThreads, 0);
     if (e != hipSuccess) return e;
-    const dim3 grid((args.max_segs + args.per_wg - 1) / args.per_wg, s.h_kv, s.n_prob);
+    const dim3 grid(args.wg_columns, s.h_kv, s.n_prob);
     if (n_wgs > (int64_t)per_cu * n_cu) {  // (the grid's other workgroups leave at once)
       *launched = false;
       return hipSuccess;

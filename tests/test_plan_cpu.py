@@ -21,7 +21,7 @@ class Shape(ctypes.Structure):
 
 class Plan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("seg_keys", "max_segs", "per_wg", "max_wgs")] + [
-        ("n_wgs", ctypes.c_int64)]
+        ("n_wgs", ctypes.c_int64), ("ragged", ctypes.c_bool)]
 
 
 def plan(lens, w, rule=EVEN, h_kv=8):
@@ -39,8 +39,9 @@ def even_segment(lens, w, h_kv=8):
     return min(max(least, seg), -(-max(lens) // 256) * 256)
 
 
-def busiest_cu(lens, keys, h_kv=8):
-    wgs = -(-max(lens) // keys)
+def busiest_cu(lens, keys, seg, h_kv=8):
+    ragged = len({-(-L // seg) for L in lens}) > 1  # then the grid's columns are odd
+    wgs = -(-max(lens) // keys) | ragged
     xcds = [[] for _ in range(8)]
     for u in range(len(lens) * h_kv):
         left = lens[u // h_kv]
@@ -67,8 +68,9 @@ def test_one_launch_leaves_no_cu_more_than_two_segments(lens, w):
     keys = p.seg_keys * p.per_wg
     assert p.max_segs == -(-max(lens) // p.seg_keys) and p.max_wgs == -(-p.max_segs // p.per_wg)
     assert p.n_wgs == sum(8 * -(-L // keys) for L in lens)
+    assert p.ragged == (len({-(-L // p.seg_keys) for L in lens}) > 1)
     if keys > seg and n_even > 256:  # a lengthened or several-segment plan
-        assert busiest_cu(lens, keys) <= 2 * seg
+        assert busiest_cu(lens, keys, p.seg_keys) <= 2 * seg
     else:  # the even plan: fits the chip, or two launches
         assert (p.seg_keys, p.per_wg) == (seg, 1)
 
