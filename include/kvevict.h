@@ -332,8 +332,10 @@ int kv_mmr_select_candidates(const kv_problem* pr, const void* ws, size_t ws_byt
  * error codes as in the two calls; nothing is launched when either would refuse its arguments.
  * Where the window kernel cuts the candidates (bf16, L_p <= 32768, see kv_window_candidates) and
  * every C_p = min(cand_mult * B_p, n_cand) <= 256, each (problem, kv head) unit's workgroup runs
- * the greedy and the compaction right after its cut, in the same launch; otherwise the two calls
- * run in turn.  Calls that overlap on one workspace race. */
+ * the greedy and the compaction right after its cut, in the same launch; where the selection kernel
+ * cuts them from the scores, one launch of it cuts, selects and compacts after the scoring; else (the
+ * window kernel's cut with C_p > 256) the two calls run in turn.  Calls that overlap on one workspace
+ * race. */
 int kv_evict_pass(const kv_problem* pr, const void* q_win, const void* k, const void* v,
                   float scale, const float* lambda1, const float* lambda2, int32_t sigma_rows,
                   int32_t budget, int32_t cand_mult, int32_t keep_tail, const kv_select_opts* opts,

@@ -72,7 +72,7 @@ struct StreamArgs {
   float* score;
   const float* lambda1;
   float w_mu;
-  // candidate mode of pass 2 (every unit one segment): per unit the candidate list,
+  // candidate mode of pass 2 (every unit one workgroup): per unit the candidate list,
   // [n_units][cand_stride] entries (the C_p candidates in position order, then 0), and the maximum
   // base score over the candidate positions clamped at 1e-12 (the selection's normaliser);
   // C_p = min(cand_mult B_p, L_p - keep_tail), B_p = budgets[p] or budget

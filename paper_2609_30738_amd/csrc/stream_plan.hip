@@ -74,7 +74,9 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
            scheduled_within(s, lens, keys, plan.columns((int)((s.max_len + keys - 1) / keys)), 2 * even);
   };
   if (s.w == 32) {
-    // four tiles per wave at least: shorter segments cost more in exchanges than they save
+    // four tiles per wave at least.  Not the fastest: mu and sigma of one layer of 4096 keys take 31 us
+    // with segments of 1024 keys, 24 with 512 and 21 with 256, of 32768 keys 43 with each; the segments
+    // are the unit of the row statistics, whose last bits shorter ones would change.
     seg = std::min(std::max<int64_t>(1024, seg), max_seg);
   } else {
     // a tile of a short window is a quarter or half of the work, so segments go down to one tile

@@ -488,11 +488,12 @@ hipError_t launch_stream_window_cands(const Shape& s, const StreamPlan& plan, co
   a.keep_tail = keep_tail;
   a.codes = codes;
   a.code_stride = cand_code_stride(s);
-  // Bounds pay where tiles outnumber candidates: at most as many tiles as candidates, and a cut
-  // that is not confined to few clusters has one in almost every tile (256 units of 8000 keys,
-  // C = 256: 287 us with bounds, 267 without; of 2000 keys 129 and 117).  Above, few tiles may
-  // suffice (16000 keys, C = 256: 257 and 442; 8000 keys, C = 128: 139 and 232), or not (10000
-  // keys, C = 256, in flat scores: 346 and 317).
+  // Bounds pay where tiles outnumber candidates and few tiles hold the best keys: with at most as many
+  // tiles as candidates, a cut that is not confined to few clusters has one in almost every tile (256
+  // units of 8000 keys, C = 256: 287 us with bounds, 267 without; of 2000 keys 129 and 117).  Above the
+  // line salient keys gain much (16000 keys, C = 256: 257 and 442; 8000 keys, C = 128: 139 and 232)
+  // and flat scores lose a tenth (10000 keys, C = 256: 346 and 317); the line is where the gain can
+  // first outweigh the loss, not where it always does.
   a.prune = s.max_len / stream::kTileKeys > cand_stride ? 1 : 0;
   if (sel) {
     a.lambda2 = sel->lambda2;

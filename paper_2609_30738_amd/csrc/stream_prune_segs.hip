@@ -173,9 +173,10 @@ template <int D, int NB, int W> struct PruneSegsLaunch {
 bool prune_segs_ok(const StreamPlan& plan, int max_cand) {
   // A workgroup's tiles must fit its tables.  Its cut rests on its own keys, so it stops early only
   // where those hold C keys above the rest: three tiles to a candidate leave room for that (about one
-  // key in a hundred).  Where they do not, most tiles are revisited: 64 units of 130000 keys in flat
-  // scores 890 us against 854 with both passes in full; at 391 tiles a workgroup (C = 256) it was
-  // 409 against 365.
+  // key in a hundred).  Where they do not, most tiles are revisited and the call takes a sixth longer
+  // than with both passes in full: 64 units of flat scores, 131072 keys 1235 us against 1047, 100001 keys
+  // 943 against 812 (with repeated passages and salient clusters 459 against 784); at 391 tiles a
+  // workgroup (C = 256) it was 409 against 365 for salient keys too.
   const int64_t tiles = (int64_t)plan.per_wg * plan.seg_keys / stream::kTileKeys;
   return plan.max_wgs > 1 && tiles <= stream::kPruneMaxTiles && tiles >= 3 * (int64_t)max_cand;
 }
