@@ -121,7 +121,7 @@ kv::StreamPlan stream_plan_of(const kv_problem* pr, const kv::Shape& s) {
 // more than once, and whole units pay even where they leave CUs idle (128 units of 30000 keys with
 // salient ones: 414 us as two workgroups each through base scores, 305 whole).  Where every second tile
 // can hold a candidate they do not (112 units of 8000 keys, C = 256: 190 and 226 us), nor where no key
-// stands out at all (128 units of 30000 keys of unit-variance noise: 437 and 700 us), which the sizes
+// stands out at all (128 units of 30000 keys of noise alone: 437 and 700 us), which the sizes
 // do not tell.
 kv::StreamPlan cand_plan_of(const kv_problem* pr, const kv::Shape& s, int max_cand) {
   return kv::stream_plan(s, pr->len_host,
