@@ -50,6 +50,7 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
     for (int p = 0; p < s.n_prob; ++p) n += s.h_kv * ((lens[p] + keys - 1) / keys);
     return n;
   };
+  const bool many_units = (int64_t)s.n_prob * s.h_kv > kCus;  // nothing fits the chip at once
   // about one segment per compute unit, whole steps
   int64_t seg = ((total + kCus - 1) / kCus + kStep - 1) / kStep * kStep;
   // Segments over the chip's CUs: one launch of longer ones (or of workgroups of several) ends when
@@ -85,7 +86,7 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
     // the chip's CUs would cost a second round: then longer segments (160 units of 2500 keys whole
     // 37 us, as 320 segments 58)
     seg = std::min(std::max<int64_t>(s.max_len <= 1024 ? 1024 : kStep, seg), max_seg);
-    int64_t longer = seg;
+    int64_t longer = many_units ? max_seg : seg;
     while (longer < max_seg && work_items(longer) > kCus)
       longer = std::min(max_seg, longer + std::max<int64_t>(kStep, longer / 16 / kStep * kStep));
     set_segments(longer);
@@ -101,6 +102,7 @@ StreamPlan stream_plan(const Shape& s, const int32_t* lens, WgRule rule) {
   if (rule == WgRule::kWhole && plan.max_segs <= kStreamMaxPerWg) {
     per_wg = plan.max_segs;
   } else {
+    if (many_units) per_wg = plan.max_segs;
     while (per_wg < plan.max_segs && work_items(seg * per_wg) > kCus) ++per_wg;
     if (per_wg > 1 && rule != WgRule::kAny && !one_launch(per_wg, seg)) per_wg = 1;
   }
